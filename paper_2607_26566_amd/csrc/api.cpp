@@ -450,7 +450,8 @@ hipError_t linear(t2i_dit* h, const void* A, int lda, int wi, int M, int N, int 
     return launch_gemm_bf16((const bf16*)A, lda, (const bf16*)W, K, (const bf16*)B, M, N, K, kind,
                             epi, allow_split ? h->at<float>(h->L.splitk) : nullptr,
                             allow_split ? h->L.splitk_floats : 0, st);
-  return launch_gemm_f32((const float*)A, lda, W, K, false, B, M, N, K, kind, epi, st);
+  return launch_gemm_f32((const float*)A, lda, (const float*)W, K, (const float*)B, M, N, K, kind,
+                         epi, st);
 }
 
 // Block b's adaLN chunks of `rows` conditioning rows (silu(c) in tsc) into
@@ -1445,8 +1446,8 @@ t2i_status t2i_op_linear(int32_t dtype, int32_t epilogue, int32_t M, int32_t N, 
   hipError_t err = dtype == T2I_BF16
                        ? launch_gemm_bf16((const bf16*)A, lda, (const bf16*)W, ldw, (const bf16*)bias,
                                           M, N, K, epilogue, e, nullptr, 0, st)
-                       : launch_gemm_f32((const float*)A, lda, W, ldw, false, bias, M, N, K,
-                                         epilogue, e, st);
+                       : launch_gemm_f32((const float*)A, lda, (const float*)W, ldw,
+                                         (const float*)bias, M, N, K, epilogue, e, st);
   if (err != hipSuccess) return ops_fail(T2I_ERR_DEVICE, hipGetErrorString(err));
   return T2I_OK;
 }

@@ -10,7 +10,8 @@
 //    one.  Workgroups are numbered so that each XCD (dispatched round-robin)
 //    receives a contiguous run of output tiles: tiles sharing A rows share
 //    that XCD's L2.
-//  * gemm_f32_kernel: SIMT fp32 FMA for the fp32 model's layers.
+//  * gemm_f32_kernel: fp32 matrix cores (v_mfma_f32_16x16x4_f32) for the fp32
+//    model's layers.
 //  * linear_rows_kernel: the conditioning GEMMs (timestep MLP, adaLN table),
 //    8 timesteps per pass, weight-streaming and HBM-bound; its per-element
 //    summation order does not depend on the number of timesteps, so a
@@ -40,6 +41,20 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
   const int q = nb >> 3, r = nb & 7;
   const int x = b & 7, j = b >> 3;
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
+}
+
+// s_waitcnt with only vmcnt constrained
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// one 16-byte-per-lane buffer load into LDS at the wave-uniform address lds
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t voff,
+                                           int soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16,
+                                           voff, soff, 0, 0);
 }
 
 // Epilogue on four consecutive columns nb..nb+3 of row m (vector path).
@@ -530,52 +545,172 @@ hipError_t launch_gemm_bf16_group(const bf16* A, int lda, const PtrGroup& g, int
 
 // ---------------------------------------------------------------------------
 
-template <typename TW, int KIND>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(
-    const float* __restrict__ A, int lda, const TW* __restrict__ W, int ldw,
-    const TW* __restrict__ bias, int M, int N, int K, Epi epi) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+// fp32 GEMM on the fp32 matrix cores (v_mfma_f32_16x16x4_f32: fp32 products,
+// fp32 accumulation), for the fp32 model's layers.  Bound by the matrix cores
+// (157 TFLOP/s fp32) at the model's 1024 rows and by load latency at the
+// smallest (64 rows).  1024 x 4608 x 1152 takes 112 us (97 TFLOP/s) where
+// vector FMAs took 213, 1024 x 1152 x 4608 128 against 620, and 64 x 128 x 512
+// 6.8 against 62.
+//
+// 4 waves as 2 x 2 own a (32 TM) x (32 TN) tile.  K advances 32 floats (128
+// bytes, 8 chunks of 16) at a time through a ring of four LDS stages filled by
+// direct loads (buffer_load_dwordx4 ... lds: 8 rows per wave instruction), the
+// 16-byte chunk c of row r in slot c ^ ((r >> 1) & 7) so that the 16 rows of a
+// fragment read spread over the banks.  A lane reads four consecutive k of its
+// row (chunk 4 kk + g) and MFMA e of the four takes component e: its k are
+// {16 kk + 4 g + e, g = 0 .. 3} for both operands, so the products are those
+// of k = 16 kk .. 16 kk + 15 and the order of the sums depends on K alone, not
+// on the tile.  DMA = false: the same tiles and sums for operands that the
+// direct loads cannot take (K % 32, unaligned rows, operands past 2 GiB),
+// staged through registers with zeros past K.
+constexpr int kF32Stages = 4;
 
-  for (int k0 = 0; k0 < K; k0 += BK) {
+template <int TM, int TN, bool DMA, int KIND>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(
+    const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
+    const float* __restrict__ bias, int M, int N, int K, Epi epi, int tiles_m, int vec_ok) {
+  constexpr int BM = 32 * TM, BN = 32 * TN, ST = DMA ? kF32Stages : 1;
+  constexpr int BPW = (BM + BN) / 32;   // direct loads per wave and stage
+  constexpr int STAGE = (BM + BN) * 32;  // floats
+  __shared__ __attribute__((aligned(1024))) float smem[ST * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 15, g = lane >> 4;
+  // row blocks vary fastest within an XCD's range of tiles: its workgroups
+  // share few W rows, and A stays in its L2
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
+  const int wm0 = (wave >> 1) * 16 * TM, wn0 = (wave & 1) * 16 * TN;
+  const int KT = (K + 31) / 32;
+
+  f32x4 acc[TM][TN];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = tid + 256 * i, r = idx >> 4, kk = idx & 15;
-      const int m = m0 + r, n = n0 + r, k = k0 + kk;
-      As[kk][r] = (m < M && k < K) ? A[(size_t)m * lda + k] : 0.f;
-      Bs[kk][r] = (n < N && k < K) ? to_f32(W[(size_t)n * ldw + k]) : 0.f;
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto frag = [&](const float* base, int row, int c) {
+    return *(const f32x4*)((const char*)base + row * 128 + ((c ^ ((row >> 1) & 7)) << 4));
+  };
+  auto compute = [&](int slot) {
+    const float* sA = smem + slot * STAGE;
+    const float* sB = sA + BM * 32;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      f32x4 af[TM], bfr[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[i] = frag(sA, wm0 + i * 16 + fr, kk * 4 + g);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bfr[j] = frag(sB, wn0 + j * 16 + fr, kk * 4 + g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bfr[j][e], af[i][e], acc[i][j], 0, 0, 0);
     }
-    __syncthreads();
+  };
+
+  if constexpr (DMA) {
+    uint32_t src[BPW];
+    const __amdgpu_buffer_rsrc_t ra =
+        __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw =
+        __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, 0x7fffffff, 0x00020000);
 #pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    for (int i = 0; i < BPW; ++i) {
+      const int blk = wave + 4 * i, lr = (i < TM ? blk : blk - BM / 8) * 8 + (lane >> 3);
+      const int c = (lane & 7) ^ ((lr >> 1) & 7);
+      // rows past the operand repeat its last one; their results are not stored
+      src[i] = 4u * (uint32_t)(i < TM ? min(m0 + lr, M - 1) * lda : min(n0 + lr, N - 1) * ldw) +
+               16u * (uint32_t)c;
     }
-    __syncthreads();
+    auto issue = [&](int t, int slot) {
+#pragma unroll
+      for (int i = 0; i < BPW; ++i)
+        load_lds16(i < TM ? ra : rw, (char*)(smem + slot * STAGE) + (wave + 4 * i) * 1024, src[i],
+                   t * 128);
+    };
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s)
+      if (s < KT) issue(s, s);
+    for (int t0 = 0; t0 < KT; t0 += ST) {
+#pragma unroll
+      for (int i = 0; i < ST; ++i) {
+        const int t = t0 + i;
+        if (t >= KT) break;
+        // stage t landed (the stages after it may fly), and every wave is done
+        // with stage t - 1, which is refilled now
+        const int younger = min(ST - 2, KT - 1 - t);
+        if (younger == 2) wait_vm<2 * BPW>();
+        else if (younger == 1) wait_vm<BPW>();
+        else wait_vm<0>();
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // this wave's LDS reads
+        asm volatile("s_barrier" ::: "memory");
+        if (t + ST - 1 < KT) issue(t + ST - 1, (i + ST - 1) % ST);
+        compute(i);
+      }
+    }
+  } else {
+    for (int t = 0; t < KT; ++t) {
+      for (int idx = tid; idx < (BM + BN) * 8; idx += 256) {
+        const int row = idx >> 3, c = idx & 7, k = t * 32 + 4 * c;
+        const bool is_a = row < BM;
+        const int lr = is_a ? row : row - BM;
+        const float* p = is_a ? A + (size_t)min(m0 + lr, M - 1) * lda
+                              : W + (size_t)min(n0 + lr, N - 1) * ldw;
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = k + e < K ? p[k + e] : 0.f;
+        *(f32x4*)((char*)smem + row * 128 + ((c ^ ((lr >> 1) & 7)) << 4)) = v;
+      }
+      __syncthreads();
+      compute(0);
+      __syncthreads();
+    }
   }
+
+  // a lane owns four consecutive columns of one row per fragment
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + wm0 + i * 16 + fr;
     if (m >= M) continue;
+    const float* grow = nullptr;
+    if constexpr (KIND == EPI_RESID_GATED)
+      grow = epi.gate + (size_t)epi.map.modrow[seq_of_row(epi.map, m)] * epi.ld_gate;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n < N) epi_apply<float>(epi, KIND, m, n, acc[i][j] + to_f32(bias[n]));
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + wn0 + j * 16 + g * 4;
+      if (vec_ok && n + 3 < N) {
+        const f32x4 b4 = *(const f32x4*)(bias + n);
+        f32x4 y;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[r] = acc[i][j][r] + b4[r];
+        if constexpr (KIND == EPI_RESID || KIND == EPI_RESID_GATED) {
+          float* xp = epi.x + (size_t)m * epi.ldx + n;
+          f32x4 x4 = *(const f32x4*)xp;
+          f32x4 g4 = f32x4{1.f, 1.f, 1.f, 1.f};
+          if constexpr (KIND == EPI_RESID_GATED) g4 = *(const f32x4*)(grow + n);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x4[r] += g4[r] * y[r];
+          *(f32x4*)xp = x4;
+          if (epi.xb)
+            *(bf16x4*)(epi.xb + (size_t)m * epi.ldx + n) =
+                bf16x4{(bf16)x4[0], (bf16)x4[1], (bf16)x4[2], (bf16)x4[3]};
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (KIND == EPI_STORE && n + r < epi.qcols) y[r] *= epi.qscale;
+            if (KIND == EPI_GELU) y[r] = gelu_tanh(y[r]);
+            if (KIND == EPI_SILU) y[r] = silu(y[r]);
+          }
+          *(f32x4*)((float*)epi.out + (size_t)m * epi.ldo + n) = y;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (n + r < N) epi_apply<float>(epi, KIND, m, n + r, acc[i][j][r] + bias[n + r]);
+      }
     }
   }
 }
@@ -719,37 +854,57 @@ hipError_t launch_linear_rows(const float* A, int lda, const void* W, int ldw, b
   return linear_rows_dispatch<float, 8>(A, lda, (const float*)W, ldw, (const float*)bias, M, N, K, kind, epi, st);
 }
 
-template <typename TW>
-static hipError_t gemm_f32_dispatch(const float* A, int lda, const TW* W, int ldw, const TW* bias,
-                                    int M, int N, int K, int kind, const Epi& epi, hipStream_t st) {
-  dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);
+template <int TM, int TN, bool DMA>
+static hipError_t gemm_f32_dispatch(const float* A, int lda, const float* W, int ldw,
+                                    const float* bias, int M, int N, int K, int kind,
+                                    const Epi& epi, int vec_ok, hipStream_t st) {
+  const int tm = (M + 32 * TM - 1) / (32 * TM), tn = (N + 32 * TN - 1) / (32 * TN);
+  dim3 grid(tm * tn), block(256);
+#define T2I_F32_CASE(K_)                                                                       \
+  case K_:                                                                                     \
+    hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, DMA, K_>), grid, block, 0, st, A, lda, W, ldw, \
+                       bias, M, N, K, epi, tm, vec_ok);                                        \
+    break;
   switch (kind) {
-    case EPI_STORE:
-      hipLaunchKernelGGL((gemm_f32_kernel<TW, EPI_STORE>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
-      break;
-    case EPI_GELU:
-      hipLaunchKernelGGL((gemm_f32_kernel<TW, EPI_GELU>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
-      break;
-    case EPI_SILU:
-      hipLaunchKernelGGL((gemm_f32_kernel<TW, EPI_SILU>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
-      break;
-    case EPI_RESID:
-      hipLaunchKernelGGL((gemm_f32_kernel<TW, EPI_RESID>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
-      break;
-    default:
-      hipLaunchKernelGGL((gemm_f32_kernel<TW, EPI_RESID_GATED>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
-      break;
+    T2I_F32_CASE(EPI_STORE)
+    T2I_F32_CASE(EPI_GELU)
+    T2I_F32_CASE(EPI_SILU)
+    T2I_F32_CASE(EPI_RESID)
+    T2I_F32_CASE(EPI_RESID_GATED)
+    default: return hipErrorInvalidValue;
   }
+#undef T2I_F32_CASE
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_f32(const float* A, int lda, const void* W, int ldw, bool w_bf16,
-                           const void* bias, int M, int N, int K, int kind, const Epi& epi,
-                           hipStream_t st) {
+hipError_t launch_gemm_f32(const float* A, int lda, const float* W, int ldw, const float* bias,
+                           int M, int N, int K, int kind, const Epi& epi, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (w_bf16)
-    return gemm_f32_dispatch<bf16>(A, lda, (const bf16*)W, ldw, (const bf16*)bias, M, N, K, kind, epi, st);
-  return gemm_f32_dispatch<float>(A, lda, (const float*)W, ldw, (const float*)bias, M, N, K, kind, epi, st);
+  auto al = [](const void* p) { return ((uintptr_t)p % 16) == 0; };
+  const int vec_ok = epi.ldo % 4 == 0 && epi.ldx % 4 == 0 && epi.ld_gate % 4 == 0 && al(bias) &&
+                     al(epi.out) && al(epi.x) && al(epi.xb) && al(epi.gate);
+  // the direct loads take whole 128-byte K steps of 16-byte aligned rows and
+  // address each operand with 32-bit byte offsets
+  const bool dma = K % 32 == 0 && lda % 4 == 0 && ldw % 4 == 0 && al(A) && al(W) &&
+                   (size_t)4 * M * lda < 0x7fffffff && (size_t)4 * N * ldw < 0x7fffffff;
+  if (!dma) {
+    if ((long)M * N <= 4096 * 1024)
+      return gemm_f32_dispatch<1, 1, false>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
+    return gemm_f32_dispatch<2, 2, false>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
+  }
+  // The CU with the most tiles decides: its tiles' K steps cost the larger of
+  // their matrix time (64 clocks per 16 x 16 x 4 MFMA group of the four waves:
+  // 256 per 32 x 32 of the tile) and their loads at ~20 bytes per clock.
+  auto cost = [&](long bm, long bn) {
+    const long tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    return ((tiles + 255) / 256) * std::max(bm * bn / 4, (bm + bn) * 128 / 20);
+  };
+  const long c22 = cost(64, 64), c12 = cost(32, 64), c11 = cost(32, 32);
+  if (c22 <= c12 && c22 <= c11)
+    return gemm_f32_dispatch<2, 2, true>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
+  if (c12 <= c11)
+    return gemm_f32_dispatch<1, 2, true>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
+  return gemm_f32_dispatch<1, 1, true>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
 }
 
 }  // namespace t2i

@@ -193,11 +193,9 @@ hipError_t launch_gemm_bf16(const bf16* A, int lda, const bf16* W, int ldw, cons
                             int M, int N, int K, int kind, const Epi& epi, float* splitk_ws,
                             size_t splitk_floats, hipStream_t st);
 
-// SIMT fp32-accumulating GEMM: A fp32, W fp32 or bf16 (w_bf16), bias like W,
-// output fp32 for STORE kinds.
-hipError_t launch_gemm_f32(const float* A, int lda, const void* W, int ldw, bool w_bf16,
-                           const void* bias, int M, int N, int K, int kind, const Epi& epi,
-                           hipStream_t st);
+// fp32 GEMM (fp32 matrix cores): A, W, bias, outputs fp32.
+hipError_t launch_gemm_f32(const float* A, int lda, const float* W, int ldw, const float* bias,
+                           int M, int N, int K, int kind, const Epi& epi, hipStream_t st);
 
 // Conditioning GEMMs: A fp32 [M, K], W fp32 or bf16 [N, K]; STORE or SILU.
 // Per-group operand table of a grouped launch (by value in the kernel

@@ -165,6 +165,55 @@ def test_linear_f32(M, N, K, epi):
         assert rel_l2(x.cpu().numpy().astype(np.float64) - x0, gate * ref) < 1e-6
 
 
+# (rows, N, K): one tile; the row and column remainders of every tile size; long K;
+# K not a whole number of 32-float steps and rows that are not 16-byte aligned
+# (both staged through registers)
+F32_TILE_SHAPES = [(1, 33, 32), (64, 128, 512), (65, 132, 96), (130, 1152, 4096), (999, 1156, 288),
+                   (1030, 4608, 128), (70, 1150, 130), (2100, 2100, 66)]
+
+
+@pytest.mark.parametrize("M,N,K", F32_TILE_SHAPES)
+def test_linear_f32_tiles(M, N, K):
+    """Every tile size and both load paths of the fp32 GEMM against float64;
+    the first rows alone (another tile size) give the same bits."""
+    say(f"linear f32 {M}x{N}x{K}")
+    A, W, b = rnd(80, (M, K), bf=False), rnd(81, (N, K), 0.05, bf=False), rnd(82, (N,), 0.1, bf=False)
+    x0 = rnd(83, (M, N), bf=False)
+    ref = dit.linear(A.astype(np.float64), W.astype(np.float64), b.astype(np.float64))
+    # sequential fp32 sums of K products: relative error about sqrt(K) * 2^-24
+    tol = 2 * np.sqrt(K) * 2.0 ** -24 + 1e-7
+    out, _, _ = run_linear(_lib.T2I_F32, _lib.T2I_EPI_STORE, A, W, b)
+    assert rel_l2(to_host(out), ref) < tol
+    _, x, xc = run_linear(_lib.T2I_F32, _lib.T2I_EPI_RESID, A, W, b, resid=x0, with_copy=True)
+    assert rel_l2(x.cpu().numpy().astype(np.float64), x0 + ref) < tol
+    assert np.array_equal(xc.float().cpu().numpy(), synth.round_bf16(x.cpu().numpy()))
+    few = max(1, M // 3)
+    part, _, _ = run_linear(_lib.T2I_F32, _lib.T2I_EPI_STORE, A[:few], W, b)
+    assert np.array_equal(part.cpu().numpy(), out.cpu().numpy()[:few])
+
+
+@pytest.mark.parametrize("d", [8, 32, 64, 72, 128])
+def test_attention_f32_tiles(d):
+    """Every head size: sequences of one query, of a query tile and one more,
+    key counts around the 64-key tile, two key segments."""
+    say(f"attention f32 d {d}")
+    H, w = 3, 3 * d
+    lens = [1, 64, 65, 127, 200]
+    seqs, seg2, row = [], [], 0
+    for i, n in enumerate(lens):
+        seqs.append((row, n, row, n))
+        seg2.append((0, 37) if i % 2 else (0, 0))
+        row += n
+    q, k, v = (rnd(84 + i, (row, w), bf=False) for i in range(3))
+    got = run_attention(_lib.T2I_F32, H, d, seqs, q, k, v, seg2)
+    for (qs, n, ks, kl), (k2, n2) in zip(seqs, seg2):
+        kk = np.concatenate([k[ks:ks + kl], k[k2:k2 + n2]]).astype(np.float64)
+        vv = np.concatenate([v[ks:ks + kl], v[k2:k2 + n2]]).astype(np.float64)
+        ref = dit.attention(q[qs:qs + n].astype(np.float64), kk, vv, H)
+        # scores of size sqrt(d) to about 2^-22 relative, the same in the weights
+        assert rel_l2(got[qs:qs + n], ref) < 2e-6
+
+
 def run_attention(dtype, heads, d, seqs, q, k, v, seg2=None):
     """seqs: (q_start, q_len, k_start, k_len); seg2: (k2_start, k2_len) per sequence."""
     lib = t2i.load()
