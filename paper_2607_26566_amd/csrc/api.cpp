@@ -386,9 +386,9 @@ bool is_mmdit(const t2i_dit* h) { return h->cfg.arch == T2I_ARCH_MMDIT; }
 hipError_t embed(t2i_dit* h, const Plan& P, const float* lat, float* x0, float* xi, int copies,
                  hipStream_t st) {
   const t2i_dit_config& c = h->cfg;
-  float2* pe = is_mmdit(h) ? nullptr : h->at<float2>(h->L.pe);
+  const float2* pe = is_mmdit(h) ? nullptr : h->at<float2>(h->L.pe);
   return launch_embed(lat, P.rm, h->w[W_PE], h->w[B_PE], h->bf(), c.hidden, c.latent_channels,
-                      c.patch, pe, P.grid_max, x0, xi, copies, st);
+                      c.patch, pe, x0, xi, copies, st);
 }
 // first residual row of the image stream
 int img_row0(const t2i_dit* h, const Plan& P) { return is_mmdit(h) ? P.txt_rows : 0; }
@@ -479,8 +479,9 @@ hipError_t block_modulation(t2i_dit* h, int b, int rows, hipStream_t st) {
   return hipSuccess;
 }
 
-// The adaLN chunks of blocks [b0, b1) in grouped launches (one group per
-// block, per stream for MMDiT); bitwise the per-block block_modulation.
+// The adaLN chunks of blocks [b0, b1) (one group per block, per stream for
+// MMDiT) and of the final layer in grouped launches; bitwise the per-block
+// block_modulation.
 hipError_t blocks_modulation(t2i_dit* h, int b0, int b1, int rows, hipStream_t st) {
   const t2i_dit_config& c = h->cfg;
   const int D = c.hidden, pb = per_block(c);
@@ -491,8 +492,9 @@ hipError_t blocks_modulation(t2i_dit* h, int b0, int b1, int rows, hipStream_t s
   e.ldo = mod_width(c);
   PtrGroup g;
   int n = 0;
-  auto flush = [&]() {
-    hipError_t err = launch_linear_rows_group(tsc, D, g, n, D, h->bf(), rows, 6 * D, D, e, st);
+  auto flush = [&](int n_last) {
+    hipError_t err =
+        launch_linear_rows_group(tsc, D, g, n, D, h->bf(), rows, 6 * D, n_last, D, e, st);
     n = 0;
     return err;
   };
@@ -504,11 +506,17 @@ hipError_t blocks_modulation(t2i_dit* h, int b0, int b1, int rows, hipStream_t s
       g.out[n] = mod + (size_t)b * (mm ? 12 : 6) * D + (size_t)s * 6 * D;
       g.vt[n] = nullptr;
       if (++n == kMaxGroups) {
-        hipError_t err = flush();
+        hipError_t err = flush(6 * D);
         if (err != hipSuccess) return err;
       }
     }
-  return flush();
+  const int fb = final_base(c);   // the final layer's [shift, scale]: the table's last 2 D columns
+  g.W[n] = h->w[fb];
+  g.bias[n] = h->w[fb + 1];
+  g.out[n] = mod + (size_t)(mod_width(c) - 2 * D);
+  g.vt[n] = nullptr;
+  ++n;
+  return flush(2 * D);
 }
 
 // The call's stream waits for block b's queued load, if any.
@@ -517,33 +525,31 @@ hipError_t wait_block(t2i_dit* h, int b, hipStream_t st) {
   return hipStreamWaitEvent(st, h->blk_ev[b], 0);
 }
 
-// Conditioning of `rows` timesteps (rows <= max_steps * max_requests):
-// silu(c) into tsc and the adaLN chunks of blocks [0, min(n_blocks_mod,
-// defer_from)) into the modulation table.
-t2i_status conditioning(t2i_dit* h, const double* t_host, int rows, int n_blocks_mod,
-                        int defer_from, hipStream_t st) {
+// The call's position table, and the conditioning of `rows` timesteps (rows <=
+// max_steps * max_requests): silu(c) into tsc and the adaLN chunks of blocks
+// [0, min(n_blocks_mod, defer_from)) and of the final layer into the
+// modulation table.
+t2i_status conditioning(t2i_dit* h, const Plan& P, const double* t_host, int rows,
+                        int n_blocks_mod, int defer_from, hipStream_t st) {
   const t2i_dit_config& c = h->cfg;
   const int D = c.hidden, fd = c.freq_dim;
   float* tfreq = h->at<float>(h->L.tfreq);
   float* th1 = h->at<float>(h->L.th1);
   float* tsc = h->at<float>(h->L.tsc);
-  float* mod = h->at<float>(h->L.mod);
   const bool wb = h->bf();
-  HIP_TRY(h, launch_timestep_freq(t_host, rows, fd, (double)c.t_scale, tfreq, st));
+  const bool mm = is_mmdit(h);
+  HIP_TRY(h, launch_call_tables(t_host, rows, fd, (double)c.t_scale, tfreq,
+                                h->at<float2>(mm ? h->L.rope : h->L.pe), P.grid_max,
+                                mm ? c.head_dim / 4 : D / 4, mm, st));
   Epi e = make_epi();
   e.out = th1;
   e.ldo = D;
   HIP_TRY(h, launch_linear_rows(tfreq, fd, h->w[W_T1], fd, wb, h->w[B_T1], rows, D, fd, EPI_SILU, e, st));
   e.out = tsc;
   HIP_TRY(h, launch_linear_rows(th1, D, h->w[W_T2], D, wb, h->w[B_T2], rows, D, D, EPI_SILU, e, st));
-  const int mw = mod_width(c);
-  e.ldo = mw;
   const int nbm = std::min(n_blocks_mod, defer_from);
   for (int b = 0; b < nbm; ++b) HIP_TRY(h, wait_block(h, b, st));
   HIP_TRY(h, blocks_modulation(h, 0, nbm, rows, st));
-  e.out = mod + (size_t)(mw - 2 * D);
-  const int fb = final_base(c);
-  HIP_TRY(h, launch_linear_rows(tsc, D, h->w[fb], D, wb, h->w[fb + 1], rows, 2 * D, D, EPI_STORE, e, st));
   return T2I_OK;
 }
 
@@ -578,13 +584,12 @@ t2i_status text_prep(t2i_dit* h, const Plan& P, const void* prompt, int nb, hipS
   e.ldo = D;
   if (is_mmdit(h)) {
     // fp32 initial text stream of every sequence (unconditional: the bias),
-    // copied into the residual at the start of each step; RoPE table
+    // copied into the residual at the start of each step
     HIP_TRY(h, linear(h, prompt, c.text_dim, W_Y, P.n_req * M, D, c.text_dim, EPI_STORE_F32, e,
                       st));
     if (P.branches == 2)
       HIP_TRY(h, launch_bias_rows_f32(h->w[B_Y], h->bf(), P.n_req * M, D,
                                       (float*)ytxt + (size_t)P.n_req * M * D, st));
-    HIP_TRY(h, launch_rope_table(h->at<float2>(h->L.rope), P.grid_max, c.head_dim / 4, st));
     return T2I_OK;
   }
   // a few hundred rows against K = text_dim: K split over workgroups
@@ -986,10 +991,11 @@ void compute_subplan(const t2i_dit* h, const Plan& P, uint32_t mask, Plan& Q, Ro
 }
 
 // Embed, blocks (or cached residual), final layer for one step whose
-// conditioning rows start at `modbase`.
+// conditioning rows start at `modbase`.  x0_ready: x0 already holds the
+// embedding of these latents (the loop's cache check).
 t2i_status step_body(t2i_dit* h, Plan& P, const float* latents_in, float* latents,
                      float* noise_pred, int nb, float* hidden_out, const uint8_t* skip,
-                     void* cache_state, hipStream_t st) {
+                     void* cache_state, bool x0_ready, hipStream_t st) {
   const t2i_dit_config& c = h->cfg;
   const int D = c.hidden;
   float* x = h->at<float>(h->L.x);
@@ -1008,7 +1014,13 @@ t2i_status step_body(t2i_dit* h, Plan& P, const float* latents_in, float* latent
                        h->L.has_xf;
   float* xi = compact ? h->at<float>(h->L.xf)
                       : x + (size_t)img_row0(h, P) * D;   // image rows, the call's layout
-  TIMED(h, T2I_K_EMBED, st, embed(h, P, latents_in, x0, xi, P.branches, st));
+  // x0 is read by the cached residual only, and where every request reuses its
+  // residual the image rows are written from x0 alone
+  const bool all_cached = cache_state && !compute_mask;
+  float* x0_out = cache_state && !x0_ready ? x0 : nullptr;
+  if (x0_out || !all_cached)
+    TIMED(h, T2I_K_EMBED, st,
+          embed(h, P, latents_in, x0_out, xi, all_cached ? 0 : P.branches, st));
   if (is_mmdit(h))
     HIP_TRY(h, hipMemcpyAsync(x, h->at<float>(h->L.ytxt), (size_t)P.txt_rows * D * 4,
                               hipMemcpyDeviceToDevice, st));
@@ -1316,10 +1328,10 @@ t2i_status t2i_dit_step(t2i_dit* h, const t2i_step_args* a, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   set_modrows(P, 0);
   P.cond_rows = P.n_req;
-  if ((s = conditioning(h, a->t, P.n_req, std::max(nb, 1), P.defer_from, st)) != T2I_OK) return s;
+  if ((s = conditioning(h, P, a->t, P.n_req, std::max(nb, 1), P.defer_from, st)) != T2I_OK) return s;
   if ((s = text_prep(h, P, a->prompt_embeds, nb, st)) != T2I_OK) return s;
   return step_body(h, P, a->latents, a->latents, a->noise_pred, nb, a->hidden_out, a->skip,
-                   a->cache_state, st);
+                   a->cache_state, false, st);
 }
 
 t2i_status t2i_cache_check(t2i_dit* h, const t2i_cache_args* a, void* stream) {
@@ -1342,7 +1354,7 @@ t2i_status t2i_cache_check(t2i_dit* h, const t2i_cache_args* a, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   set_modrows(P, 0);
   // block 0's modulation only: a loading block 0 is waited for in place
-  if ((s = conditioning(h, a->t, P.n_req, 1, INT_MAX, st)) != T2I_OK) return s;
+  if ((s = conditioning(h, P, a->t, P.n_req, 1, INT_MAX, st)) != T2I_OK) return s;
   HIP_TRY(h, embed(h, P, a->latents, h->at<float>(h->L.x0), h->at<float>(h->L.x), 0, st));
   return cache_check_impl(h, P, a->step, a->n_steps, a->tau, a->mode, a->cache_state, a->rel_l1,
                           a->skip, st);
@@ -1377,7 +1389,7 @@ t2i_status t2i_dit_sample(t2i_dit* h, const t2i_sample_args* a, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   // conditioning rows k*R + r for every step k < n
   P.cond_rows = n * R;
-  if ((s = conditioning(h, ts.data(), n * R, c.depth, P.defer_from, st)) != T2I_OK) return s;
+  if ((s = conditioning(h, P, ts.data(), n * R, c.depth, P.defer_from, st)) != T2I_OK) return s;
   if ((s = text_prep(h, P, a->prompt_embeds, c.depth, st)) != T2I_OK) return s;
   std::vector<uint8_t> skip(R, 0);
   std::vector<double> rel(R, 0.0);
@@ -1398,7 +1410,7 @@ t2i_status t2i_dit_sample(t2i_dit* h, const t2i_sample_args* a, void* stream) {
     }
     if ((s = step_body(h, P, a->latents, a->latents, nullptr, c.depth, nullptr,
                        use_cache ? skip.data() : nullptr, use_cache ? a->cache_state : nullptr,
-                       st)) != T2I_OK)
+                       use_cache, st)) != T2I_OK)
       return s;
   }
   return T2I_OK;

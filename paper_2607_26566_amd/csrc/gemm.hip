@@ -722,12 +722,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(
 // to MT activation rows (fp32, L2-resident), and reduce across the wave.
 // Weight reads are contiguous 1 KB per wave instruction.
 
-template <typename TW, int MT, int KIND>
+// NC columns per wave; all loads of a step (weights, then every row, rows past
+// the last repeated) are issued before its arithmetic, so that they cost one
+// latency and not one per row (1152 x 1152: 13.9 -> 7.1 us for 5 rows, 19.8 ->
+// 11.0 for 20, with one column per wave 6.4 -> 5.1 for one).
+template <typename TW, int MT, int NC, int KIND>
 __device__ __forceinline__ void linear_rows_body(const float* __restrict__ A, int lda,
                                                  const TW* __restrict__ W, int ldw,
                                                  const TW* __restrict__ bias, int M, int N, int K,
                                                  const Epi& epi) {
-  constexpr int NC = 4;
   const int lane = threadIdx.x & 63;
   const int n0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * NC;
   const int m0 = blockIdx.x * MT;
@@ -738,8 +741,10 @@ __device__ __forceinline__ void linear_rows_body(const float* __restrict__ A, in
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int j = 0; j < NC; ++j) acc[m][j] = 0.f;
+#pragma unroll(NC == 1 && MT <= 2 ? 4 : 1)
   for (int k = lane * 8; k < K; k += 64 * 8) {
     float wv[NC][8];
+    float4 a[MT], b[MT];
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
       const int n = min(n0 + j, N - 1);
@@ -756,10 +761,14 @@ __device__ __forceinline__ void linear_rows_body(const float* __restrict__ A, in
     }
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
+      const float* ap = A + (size_t)(m0 + min(m, mt - 1)) * lda + k;
+      a[m] = *(const float4*)ap;
+      b[m] = *(const float4*)(ap + 4);
+    }
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
       if (m < mt) {
-        const float* ap = A + (size_t)(m0 + m) * lda + k;
-        const float4 a = *(const float4*)ap, b = *(const float4*)(ap + 4);
-        const float av[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        const float av[8] = {a[m].x, a[m].y, a[m].z, a[m].w, b[m].x, b[m].y, b[m].z, b[m].w};
 #pragma unroll
         for (int j = 0; j < NC; ++j)
 #pragma unroll
@@ -778,12 +787,12 @@ __device__ __forceinline__ void linear_rows_body(const float* __restrict__ A, in
   }
 }
 
-template <typename TW, int MT, int KIND>
+template <typename TW, int MT, int NC, int KIND>
 __global__ __launch_bounds__(256) void linear_rows_kernel(const float* __restrict__ A, int lda,
                                                           const TW* __restrict__ W, int ldw,
                                                           const TW* __restrict__ bias, int M,
                                                           int N, int K, Epi epi) {
-  linear_rows_body<TW, MT, KIND>(A, lda, W, ldw, bias, M, N, K, epi);
+  linear_rows_body<TW, MT, NC, KIND>(A, lda, W, ldw, bias, M, N, K, epi);
 }
 
 // Several weight matrices against the same rows in one launch: group
@@ -791,25 +800,36 @@ __global__ __launch_bounds__(256) void linear_rows_kernel(const float* __restric
 template <typename TW, int MT, int KIND>
 __global__ __launch_bounds__(256) void linear_rows_group_kernel(const float* __restrict__ A,
                                                                 int lda, PtrGroup g, int ldw,
-                                                                int M, int N, int K, Epi epi) {
+                                                                int M, int N, int n_last, int K,
+                                                                Epi epi) {
   const int grp = blockIdx.z;
   epi.out = g.out[grp];
-  linear_rows_body<TW, MT, KIND>(A, lda, (const TW*)g.W[grp], ldw, (const TW*)g.bias[grp], M, N,
-                                 K, epi);
+  linear_rows_body<TW, MT, 4, KIND>(A, lda, (const TW*)g.W[grp], ldw, (const TW*)g.bias[grp], M,
+                                    grp + 1 == (int)gridDim.z ? n_last : N, K, epi);
 }
+
+// Rows per weight pass: as few as hold M (fewer registers, so more waves
+// stream weights at once), at most 8.  Each row's sums are the same in all.
+inline int rows_per_pass(int M) { return M <= 2 ? 2 : M <= 4 ? 4 : 8; }
 
 template <typename TW, int MT>
 static hipError_t linear_rows_dispatch(const float* A, int lda, const TW* W, int ldw,
                                        const TW* bias, int M, int N, int K, int kind,
                                        const Epi& epi, hipStream_t st) {
-  // consecutive workgroups share weight rows (row passes vary fastest)
-  dim3 grid((M + MT - 1) / MT, (N + 15) / 16), block(256);
+  // consecutive workgroups share weight rows (row passes vary fastest).  Four
+  // columns per wave read the rows once for all of them, but up to 4096
+  // columns (the timestep MLP) that leaves most CUs idle: one there
+  const int nc = N > 4096 && kind == EPI_STORE ? 4 : 1;
+  dim3 grid((M + MT - 1) / MT, (N + 4 * nc - 1) / (4 * nc)), block(256);
   switch (kind) {
     case EPI_STORE:
-      hipLaunchKernelGGL((linear_rows_kernel<TW, MT, EPI_STORE>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
+      if (nc == 4)
+        hipLaunchKernelGGL((linear_rows_kernel<TW, MT, 4, EPI_STORE>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
+      else
+        hipLaunchKernelGGL((linear_rows_kernel<TW, MT, 1, EPI_STORE>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
       break;
     case EPI_SILU:
-      hipLaunchKernelGGL((linear_rows_kernel<TW, MT, EPI_SILU>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
+      hipLaunchKernelGGL((linear_rows_kernel<TW, MT, 1, EPI_SILU>), grid, block, 0, st, A, lda, W, ldw, bias, M, N, K, epi);
       break;
     default:
       return hipErrorInvalidValue;
@@ -818,27 +838,28 @@ static hipError_t linear_rows_dispatch(const float* A, int lda, const TW* W, int
 }
 
 hipError_t launch_linear_rows_group(const float* A, int lda, const PtrGroup& g, int groups,
-                                    int ldw, bool w_bf16, int M, int N, int K, const Epi& epi,
-                                    hipStream_t st) {
+                                    int ldw, bool w_bf16, int M, int N, int n_last, int K,
+                                    const Epi& epi, hipStream_t st) {
   if (groups <= 0 || M <= 0 || N <= 0) return hipSuccess;
-  if (groups > kMaxGroups || K % 8 || lda % 4 || ldw % 8 || ((uintptr_t)A & 15))
+  if (groups > kMaxGroups || n_last > N || K % 8 || lda % 4 || ldw % 8 || ((uintptr_t)A & 15))
     return hipErrorInvalidValue;
   for (int i = 0; i < groups; ++i)
     if ((uintptr_t)g.W[i] & 15) return hipErrorInvalidValue;
-  dim3 grid((M + 7) / 8, (N + 15) / 16, groups), block(256);
-  if (w_bf16 && M <= 2) {
-    // one step's conditioning rows: a 2-row instance needs fewer registers,
-    // so more waves stream weights at once (each row's sums are those of the
-    // 8-row instance)
-    grid.x = 1;
-    hipLaunchKernelGGL((linear_rows_group_kernel<bf16, 2, EPI_STORE>), grid, block, 0, st, A, lda,
-                       g, ldw, M, N, K, epi);
-  } else if (w_bf16)
-    hipLaunchKernelGGL((linear_rows_group_kernel<bf16, 8, EPI_STORE>), grid, block, 0, st, A, lda,
-                       g, ldw, M, N, K, epi);
-  else
-    hipLaunchKernelGGL((linear_rows_group_kernel<float, 8, EPI_STORE>), grid, block, 0, st, A, lda,
-                       g, ldw, M, N, K, epi);
+  const int mt = rows_per_pass(M);
+  dim3 grid((M + mt - 1) / mt, (N + 15) / 16, groups), block(256);
+#define T2I_ROWS(TW_, MT_)                                                                      \
+  hipLaunchKernelGGL((linear_rows_group_kernel<TW_, MT_, EPI_STORE>), grid, block, 0, st, A, lda, \
+                     g, ldw, M, N, n_last, K, epi)
+  if (w_bf16) {
+    if (mt == 2) T2I_ROWS(bf16, 2);
+    else if (mt == 4) T2I_ROWS(bf16, 4);
+    else T2I_ROWS(bf16, 8);
+  } else {
+    if (mt == 2) T2I_ROWS(float, 2);
+    else if (mt == 4) T2I_ROWS(float, 4);
+    else T2I_ROWS(float, 8);
+  }
+#undef T2I_ROWS
   return hipGetLastError();
 }
 
@@ -849,9 +870,19 @@ hipError_t launch_linear_rows(const float* A, int lda, const void* W, int ldw, b
   if ((kind != EPI_STORE && kind != EPI_SILU) || K % 8 || lda % 4 || ldw % 8 ||
       ((uintptr_t)A & 15) || ((uintptr_t)W & 15))
     return hipErrorInvalidValue;
-  if (w_bf16)
-    return linear_rows_dispatch<bf16, 8>(A, lda, (const bf16*)W, ldw, (const bf16*)bias, M, N, K, kind, epi, st);
-  return linear_rows_dispatch<float, 8>(A, lda, (const float*)W, ldw, (const float*)bias, M, N, K, kind, epi, st);
+#define T2I_ROWS(TW_, MT_)                                                                       \
+  return linear_rows_dispatch<TW_, MT_>(A, lda, (const TW_*)W, ldw, (const TW_*)bias, M, N, K, kind, \
+                                        epi, st)
+  const int mt = rows_per_pass(M);
+  if (w_bf16) {
+    if (mt == 2) T2I_ROWS(bf16, 2);
+    if (mt == 4) T2I_ROWS(bf16, 4);
+    T2I_ROWS(bf16, 8);
+  }
+  if (mt == 2) T2I_ROWS(float, 2);
+  if (mt == 4) T2I_ROWS(float, 4);
+  T2I_ROWS(float, 8);
+#undef T2I_ROWS
 }
 
 template <int TM, int TN, bool DMA>

@@ -225,174 +225,257 @@ hipError_t launch_ln_modulate(bool bf16_out, int rows, int D, const float* x, in
 // ---------------------------------------------------------------------------
 // Patchify + patch embedding (+ 2D sin-cos position embedding).
 // Token i*(w/p)+j of a request reads latent [c, i*p+a, j*p+b] as feature
-// (a*p+b)*C+c.  Writes x0 (one copy) and `copies` copies into x (one per
-// guidance branch, branch-major).
+// (a*p+b)*C+c.  Writes x0 (one copy, unless NULL) and `copies` copies into x
+// (one per guidance branch, branch-major).
 //
-// pe_table_kernel: tab[pos * qd + f] = (sin, cos)(pos * 10000^(-f/qd)) in fp64,
-// qd = D/4.  embed_kernel: a workgroup takes kEmbTok tokens x 256 channels;
-// the tokens' patches are staged in LDS, each thread keeps its channel's
-// weight row in registers.  The first D/2 channels add the row's sin-cos
-// embedding, the last D/2 the column's; within a half the first D/4 are sin,
-// the next D/4 cos.
+// The position table (launch_call_tables) holds (sin, cos)(pos * 10000^(-f/qd)),
+// qd = D/4.  The first D/2 channels add the row's sin-cos embedding, the last
+// D/2 the column's; within a half the first D/4 are sin, the next D/4 cos.
 
-__global__ void pe_table_kernel(float2* __restrict__ tab, int npos, int qd) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= npos * qd) return;
-  const int pos = i / qd, f = i - pos * qd;
-  const double ang = (double)pos * pow(10000.0, -(double)f / (double)qd);
-  tab[i] = float2{(float)sin(ang), (float)cos(ang)};
+// embed_mfma_kernel (P a multiple of 16): a workgroup takes 16 tokens x 16 ET
+// channels per wave on v_mfma_f32_16x16x4_f32 (fp32 patches, weights widened to
+// fp32).  The patches are gathered into LDS once and kept in registers as the
+// token operand; with the weights as the row operand a lane ends with four
+// consecutive channels of one token; the tile leaves along the rows.  Bound by the stores:
+// 14 us at 4096 tokens x 2 branches of width 1152 (one channel per thread with
+// the patches read from LDS: 16.6), 48 at 4096 tokens of width 3072 (53).
+// embed_kernel: any other P <= 64, one channel per thread.
+
+// the 16-token patch gather both kernels start with: patch[t][(a p + b) C + c],
+// and each token's grid position
+template <int TOK, int PITCH>
+struct EmbedTokens {
+  float patch[TOK][PITCH];
+  long long base[TOK];
+  int w[TOK], hw[TOK], pos[TOK][2];
+};
+
+template <int TOK, int PITCH>
+__device__ __forceinline__ void gather_patches(EmbedTokens<TOK, PITCH>& e, const float* lat,
+                                               const ReqMap& rm, int t0, int P, int C, int p) {
+  // each token's patch origin in its request's latent, once
+  if (threadIdx.x < TOK) {
+    const int t = threadIdx.x, tok = t0 + t;
+    long long base = -1;
+    int W = 0, HW = 0, gi = 0, gj = 0;
+    if (tok < rm.tokens_total) {
+      const int r = req_of_token(rm, tok);
+      const int lt = tok - rm.tok_off[r];
+      W = rm.w[r];
+      HW = rm.h[r] * W;
+      const int gw = W / p;
+      gi = lt / gw;
+      gj = lt - gi * gw;
+      base = rm.lat_off[r] + (long long)(gi * p) * W + gj * p;
+    }
+    e.pos[t][0] = gi;
+    e.pos[t][1] = gj;
+    e.base[t] = base;
+    e.w[t] = W;
+    e.hw[t] = HW;
+  }
+  __syncthreads();
+  // element (t, k = (a p + b) C + c) in the order (c, a, t, b): the pixels of
+  // neighbouring threads are neighbours in a latent row
+  for (int i = threadIdx.x; i < TOK * P; i += 256) {
+    const int b = i % p, rest = i / p;
+    const int t = rest % TOK, ca = rest / TOK;
+    const int a = ca % p, c = ca / p;
+    float v = 0.f;
+    if (e.base[t] >= 0) v = lat[e.base[t] + (long long)c * e.hw[t] + (long long)a * e.w[t] + b];
+    e.patch[t][(a * p + b) * C + c] = v;
+  }
+  __syncthreads();
 }
 
-// 8 tokens per workgroup: 2560 workgroups for 4096 tokens (measured against
-// 32: 29.5 -> 24.8 us at 4096 tokens x 2 branches, 23.7 -> 13.7 us at 1024
-// tokens), the stores spread evenly over the CUs
+// KC: P / 16.  x0 may be NULL (no copy wanted besides x).
+template <typename TW, int KC, int ET>
+__global__ __launch_bounds__(256) void embed_mfma_kernel(const float* __restrict__ lat, ReqMap rm,
+                                                         const TW* __restrict__ w_pe,
+                                                         const TW* __restrict__ b_pe, int D, int C,
+                                                         int p, const float2* __restrict__ pe,
+                                                         float* __restrict__ x0,
+                                                         float* __restrict__ x, int copies) {
+  constexpr int P = 16 * KC;
+  __shared__ __attribute__((aligned(16))) EmbedTokens<16, P + 4> es;
+  const int lane = threadIdx.x & 63, fr = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int T = rm.tokens_total, t0 = blockIdx.y * 16;
+  const int qd = D / 4, d00 = (blockIdx.x * 4 + wave) * ET * 16;
+  // the wave's weights and biases, fetched while the patches are gathered
+  // (channel tiles past D repeat the last one and are not stored)
+  float w[ET][KC][4], add[ET][4];
+#pragma unroll
+  for (int j = 0; j < ET; ++j) {
+    const int d0 = min(d00 + j * 16, D - 16);
+    const TW* wr = w_pe + (size_t)(d0 + fr) * P + 4 * g;
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      if constexpr (sizeof(TW) == 2) {
+        const bf16x4 q = *(const bf16x4*)(wr + 16 * c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[j][c][e] = (float)q[e];
+      } else {
+        const f32x4 q = *(const f32x4*)(wr + 16 * c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[j][c][e] = q[e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) add[j][e] = to_f32(b_pe[d0 + 4 * g + e]);
+  }
+  gather_patches(es, lat, rm, t0, P, C, p);
+  f32x4 pf[KC];
+#pragma unroll
+  for (int c = 0; c < KC; ++c) pf[c] = *(const f32x4*)&es.patch[fr][16 * c + 4 * g];
+  float pos[ET][4];
+  if (pe) {
+    // D / 4 is a multiple of 16: a lane's four channels lie in one of the four
+    // parts (row sin, row cos, column sin, column cos)
+#pragma unroll
+    for (int j = 0; j < ET; ++j) {
+      const int d = min(d00 + j * 16, D - 16) + 4 * g;
+      const int part = d / qd, f = d - part * qd;
+      const float4* sc = (const float4*)(pe + (size_t)es.pos[fr][part >> 1] * qd + f);
+      const float4 s0 = sc[0], s1 = sc[1];
+      pos[j][0] = part & 1 ? s0.y : s0.x;
+      pos[j][1] = part & 1 ? s0.w : s0.z;
+      pos[j][2] = part & 1 ? s1.y : s1.x;
+      pos[j][3] = part & 1 ? s1.w : s1.z;
+    }
+  }
+  // the wave's 16 tokens x 16 ET channels through its own part of LDS, so that
+  // they go out along the rows (a fragment's store would write 16 rows x 64
+  // bytes)
+  constexpr int SP = 16 * ET + 4;
+  __shared__ __attribute__((aligned(16))) float stage[4][16 * SP];
+  float* const sw = stage[wave];
+#pragma unroll
+  for (int j = 0; j < ET; ++j) {
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][c][e], pf[c][e], acc, 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      acc[e] += add[j][e];
+      if (pe) acc[e] += pos[j][e];
+    }
+    *(f32x4*)&sw[fr * SP + j * 16 + 4 * g] = acc;
+  }
+#pragma unroll
+  for (int i = 0; i < ET; ++i) {
+    const int idx = i * 64 + lane, t = idx / (4 * ET), c = 4 * (idx - t * 4 * ET);
+    if (t0 + t < T && d00 + c < D) {
+      const f32x4 y = *(const f32x4*)&sw[t * SP + c];
+      const size_t o = (size_t)(t0 + t) * D + d00 + c;
+      if (x0) *(f32x4*)(x0 + o) = y;
+      for (int cp = 0; cp < copies; ++cp) *(f32x4*)(x + (size_t)cp * T * D + o) = y;
+    }
+  }
+}
+
+// 8 tokens per workgroup, one channel per thread, its weight row in registers
 constexpr int kEmbTok = 8;
 
-// PT: patch features p*p*C known at compile time (16, 64), else 0 (any
-// P <= 64): with constant trip counts the weights load as 16-byte vectors and
-// the patch rows as float4, with no per-feature branches.
-template <typename TW, int PT>
+template <typename TW>
 __global__ __launch_bounds__(256) void embed_kernel(const float* __restrict__ lat, ReqMap rm,
                                                     const TW* __restrict__ w_pe,
                                                     const TW* __restrict__ b_pe, int D, int C,
                                                     int p, const float2* __restrict__ pe,
                                                     float* __restrict__ x0, float* __restrict__ x,
                                                     int copies) {
-  // rows padded to 68 floats: 16-byte aligned, and neighbouring rows start
-  // four banks apart
-  __shared__ __attribute__((aligned(16))) float patch[kEmbTok][68];
-  __shared__ int grid_pos[kEmbTok][2];
-  __shared__ long long tok_base[kEmbTok];
-  __shared__ int tok_w[kEmbTok], tok_hw[kEmbTok];
-  const int P = PT ? PT : p * p * C;
+  __shared__ __attribute__((aligned(16))) EmbedTokens<kEmbTok, 68> es;
+  const int P = p * p * C;
   const int T = rm.tokens_total;
   const int t0 = blockIdx.x * kEmbTok, d = blockIdx.y * 256 + threadIdx.x;
-  // each token's patch origin in its request's latent, once
-  if (threadIdx.x < kEmbTok) {
-    const int t = threadIdx.x, tok = t0 + t;
-    long long base = -1;
-    int W = 0, HW = 0;
-    if (tok < T) {
-      const int r = req_of_token(rm, tok);
-      const int lt = tok - rm.tok_off[r];
-      W = rm.w[r];
-      HW = rm.h[r] * W;
-      const int gw = W / p, gi = lt / gw, gj = lt - gi * gw;
-      base = rm.lat_off[r] + (long long)(gi * p) * W + gj * p;
-      grid_pos[t][0] = gi;
-      grid_pos[t][1] = gj;
-    }
-    tok_base[t] = base;
-    tok_w[t] = W;
-    tok_hw[t] = HW;
-  }
-  __syncthreads();
-  // gather element (t, k = (a p + b) C + c) in the order (c, a, t, b): the
-  // pixels of neighbouring threads are neighbours in a latent row
-  for (int i = threadIdx.x; i < kEmbTok * P; i += 256) {
-    const int b = i % p, rest = i / p;
-    const int t = rest % kEmbTok, ca = rest / kEmbTok;
-    const int a = ca % p, c = ca / p;
-    float v = 0.f;
-    if (tok_base[t] >= 0)
-      v = lat[tok_base[t] + (long long)c * tok_hw[t] + (long long)a * tok_w[t] + b];
-    patch[t][(a * p + b) * C + c] = v;
-  }
-  __syncthreads();
+  gather_patches(es, lat, rm, t0, P, C, p);
   if (d >= D) return;
-  constexpr int NW = PT ? PT : 64;
-  float w[NW];
-  if constexpr (PT > 0 && sizeof(TW) == 2) {
+  float w[64];
 #pragma unroll
-    for (int k8 = 0; k8 < PT / 8; ++k8) {
-      const bf16x8 q = *(const bf16x8*)(w_pe + (size_t)d * PT + 8 * k8);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) w[8 * k8 + e] = (float)q[e];
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < NW; ++k) w[k] = k < P ? to_f32(w_pe[(size_t)d * P + k]) : 0.f;
-  }
+  for (int k = 0; k < 64; ++k) w[k] = k < P ? to_f32(w_pe[(size_t)d * P + k]) : 0.f;
   const float bias = to_f32(b_pe[d]);
   const int half = D / 2, qd = D / 4, kk = d % half, f = kk % qd;
   for (int t = 0; t < kEmbTok; ++t) {
     const int tok = t0 + t;
     if (tok >= T) break;
     float acc = bias;
-    if constexpr (PT > 0) {
 #pragma unroll
-      for (int k4 = 0; k4 < PT / 4; ++k4) {
-        const float4 pv = *(const float4*)&patch[t][4 * k4];
-        acc = fmaf(w[4 * k4 + 0], pv.x, acc);
-        acc = fmaf(w[4 * k4 + 1], pv.y, acc);
-        acc = fmaf(w[4 * k4 + 2], pv.z, acc);
-        acc = fmaf(w[4 * k4 + 3], pv.w, acc);
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < 64; ++k)
-        if (k < P) acc = fmaf(w[k], patch[t][k], acc);
-    }
+    for (int k = 0; k < 64; ++k)
+      if (k < P) acc = fmaf(w[k], es.patch[t][k], acc);
     if (pe) {
-      const float2 sc = pe[grid_pos[t][d < half ? 0 : 1] * qd + f];
+      const float2 sc = pe[es.pos[t][d < half ? 0 : 1] * qd + f];
       acc += kk < qd ? sc.x : sc.y;
     }
-    x0[(size_t)tok * D + d] = acc;
+    if (x0) x0[(size_t)tok * D + d] = acc;
     for (int cp = 0; cp < copies; ++cp) x[((size_t)cp * T + tok) * D + d] = acc;
   }
 }
 
 hipError_t launch_embed(const float* lat, const ReqMap& rm, const void* w_pe, const void* b_pe,
-                        bool w_bf16, int D, int C, int p, float2* pe_table, int pe_npos,
-                        float* x0, float* x, int copies, hipStream_t st) {
+                        bool w_bf16, int D, int C, int p, const float2* pe_table, float* x0,
+                        float* x, int copies, hipStream_t st) {
   if (rm.tokens_total == 0) return hipSuccess;
-  if (pe_table) {
-    const int n = pe_npos * (D / 4);
-    hipLaunchKernelGGL(pe_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, pe_table, pe_npos,
-                       D / 4);
-  }
-  dim3 grid((rm.tokens_total + kEmbTok - 1) / kEmbTok, (D + 255) / 256);
-  const int P = p * p * C;
-#define T2I_EMB(TW_, PT_)                                                                     \
-  hipLaunchKernelGGL((embed_kernel<TW_, PT_>), grid, dim3(256), 0, st, lat, rm, (const TW_*)w_pe, \
+  const int P = p * p * C, T = rm.tokens_total;
+#define T2I_EMB(K_, TW_, GX_, GY_)                                                             \
+  hipLaunchKernelGGL(K_, dim3(GX_, GY_), dim3(256), 0, st, lat, rm, (const TW_*)w_pe,          \
                      (const TW_*)b_pe, D, C, p, pe_table, x0, x, copies)
+  // 6 channel tiles per wave (1152 channels: 3 workgroups per 16 tokens)
+  constexpr int ET = 6;
+  const int gx = (T + 15) / 16, gy = (D + 64 * ET - 1) / (64 * ET);
+  // (aligned weight rows, 16-byte vectors of the outputs)
+  const bool mf = (uintptr_t)w_pe % 16 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)x0 % 16 == 0;
+#define T2I_EMB_ANY(TW_)                                                                       \
+  if (P == 16 && mf) T2I_EMB((embed_mfma_kernel<TW_, 1, ET>), TW_, gy, gx);                    \
+  else if (P == 64 && mf) T2I_EMB((embed_mfma_kernel<TW_, 4, ET>), TW_, gy, gx);               \
+  else T2I_EMB((embed_kernel<TW_>), TW_, (T + kEmbTok - 1) / kEmbTok, (D + 255) / 256)
   if (w_bf16) {
-    if (P == 16) T2I_EMB(bf16, 16);
-    else if (P == 64) T2I_EMB(bf16, 64);
-    else T2I_EMB(bf16, 0);
+    T2I_EMB_ANY(bf16);
   } else {
-    if (P == 16) T2I_EMB(float, 16);
-    else T2I_EMB(float, 0);
+    T2I_EMB_ANY(float);
   }
+#undef T2I_EMB_ANY
 #undef T2I_EMB
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// Timestep sinusoid: row r, s = t_scale * t[r]: [cos(s f_k) | sin(s f_k)],
-// f_k = exp(-ln(10000) k / half), evaluated in fp64.
+// Per-call tables, in fp64 and one launch (they depend on the call's arguments
+// only): the timestep sinusoid, row r with s = t_scale * t[r]: [cos(s f_k) |
+// sin(s f_k)], f_k = exp(-ln(10000) k / half); and the position table of npos
+// grid positions, tab[pos * q + f] from the angle pos * 10000^(-f/q): (sin,
+// cos) for the additive embedding, (cos, sin) for RoPE (cos_first).
 
-__global__ void timestep_freq_kernel(TVals tv, int freq_dim, double t_scale,
-                                     float* __restrict__ out) {
-  const int half = freq_dim / 2;
+__global__ void call_tables_kernel(TVals tv, int freq_dim, double t_scale, float* __restrict__ out,
+                                   float2* __restrict__ tab, int npos, int q, int cos_first) {
+  const int nt = tv.n * freq_dim, half = freq_dim / 2;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= tv.n * freq_dim) return;
-  const int r = idx / freq_dim, k = idx - r * freq_dim;
-  const int kk = k < half ? k : k - half;
-  const double f = exp(-log(10000.0) * (double)kk / (double)half);
-  const double a = t_scale * tv.t[r] * f;
-  out[idx] = (float)(k < half ? cos(a) : sin(a));
+  if (idx < nt) {
+    const int r = idx / freq_dim, k = idx - r * freq_dim;
+    const int kk = k < half ? k : k - half;
+    const double f = exp(-log(10000.0) * (double)kk / (double)half);
+    const double a = t_scale * tv.t[r] * f;
+    out[idx] = (float)(k < half ? cos(a) : sin(a));
+  } else if (idx - nt < npos * q) {
+    const int i = idx - nt, pos = i / q, f = i - pos * q;
+    const double ang = (double)pos * pow(10000.0, -(double)f / (double)q);
+    const float sn = (float)sin(ang), cs = (float)cos(ang);
+    tab[i] = cos_first ? float2{cs, sn} : float2{sn, cs};
+  }
 }
 
-hipError_t launch_timestep_freq(const double* t, int rows, int freq_dim, double t_scale,
-                                float* out, hipStream_t st) {
+hipError_t launch_call_tables(const double* t, int rows, int freq_dim, double t_scale, float* out,
+                              float2* tab, int npos, int q, bool cos_first, hipStream_t st) {
   for (int r0 = 0; r0 < rows; r0 += kTValsChunk) {
     TVals tv;
     tv.n = std::min(kTValsChunk, rows - r0);
     for (int i = 0; i < tv.n; ++i) tv.t[i] = t[r0 + i];
-    const int n = tv.n * freq_dim;
-    hipLaunchKernelGGL(timestep_freq_kernel, dim3((n + 255) / 256), dim3(256), 0, st, tv, freq_dim,
-                       t_scale, out + (size_t)r0 * freq_dim);
+    const int np = r0 == 0 ? npos : 0;   // the position table with the first chunk
+    const int n = tv.n * freq_dim + np * q;
+    hipLaunchKernelGGL(call_tables_kernel, dim3((n + 255) / 256), dim3(256), 0, st, tv, freq_dim,
+                       t_scale, out + (size_t)r0 * freq_dim, tab, np, q, cos_first ? 1 : 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -424,21 +507,6 @@ hipError_t launch_broadcast_rows(const void* src, bool bf16_io, int rows, int D,
 
 // ---------------------------------------------------------------------------
 // 2D rotary position embedding of the image tokens (joint-attention model).
-
-__global__ void rope_table_kernel(float2* __restrict__ tab, int npos, int q) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= npos * q) return;
-  const int pos = i / q, j = i - pos * q;
-  const double ang = (double)pos * pow(10000.0, -(double)j / (double)q);
-  tab[i] = float2{(float)cos(ang), (float)sin(ang)};
-}
-
-hipError_t launch_rope_table(float2* table, int npos, int q, hipStream_t st) {
-  const int n = npos * q;
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, table, npos, q);
-  return hipGetLastError();
-}
 
 // one thread per (row, head, half, pair): rotates the q pair and the k pair
 __global__ void rope_apply_kernel(bf16* __restrict__ qk, int ld, int row0, ReqMap rm, int heads,
@@ -776,170 +844,39 @@ hipError_t launch_bias_rows_f32(const void* bias, bool bias_bf16, int rows, int 
 // Final layer: per image token and guidance branch,
 //   out = LNmod(x; shift, scale) W_out^T + b_out     (P = p*p*C outputs)
 // then v = v_u + g (v_c - v_u), unpatchify, noise_pred = v, latent += dt v.
-// One wave per token, both guidance branches together (each weight load
-// serves both).  Each lane accumulates its share of every output (same
-// per-lane FMA order as a per-output loop); for P a power of two the P sums
-// are then finished by one butterfly reduce-scatter whose pairings are those
-// of wave_sum, so every output is added up in exactly the same order.
-template <typename TW, int PT>
-__device__ __forceinline__ float4 ld_w4(const TW* w) {
+//
+// final_mfma_kernel (P = 16 or 64): a workgroup of 8 waves takes 16 tokens in
+// all NB guidance branches.  A wave holds 2 NB rows in registers (one
+// coalesced read), takes their LayerNorm statistics in two passes, and writes
+// the modulated rows to LDS, CH columns at a time; the waves then share the
+// contraction of those columns: wave w takes the 32-column steps w, w + 8, ...
+// for all tokens, branches and outputs on v_mfma_f32_16x16x4_f32 (fp32 rows
+// against the weights widened to fp32).  The waves' sums are added in wave
+// order.  Bound by reading the rows (and, at P = 64, the projection once per
+// 16 tokens from L2).  Against one wave per token (P = 16) or a 32-token
+// register tile (P = 64) on vector FMAs: 28.4 -> 19.2 us at 4096 tokens x 2
+// branches and 37.4 -> 18.7 at 8168 x 1 (width 1152), 220 -> 44 at 4096 tokens
+// of width 3072; 13 us either way at 1024 tokens.
+
+template <typename TW>
+__device__ __forceinline__ void ld_w8(const TW* w, float (&o)[8]) {
   if constexpr (sizeof(TW) == 2) {
-    const bf16x4 q = *(const bf16x4*)w;
-    return float4{(float)q[0], (float)q[1], (float)q[2], (float)q[3]};
+    const bf16x8 q = *(const bf16x8*)w;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = (float)q[e];
   } else {
-    return *(const float4*)w;
+    const float4 a = *(const float4*)w, b = *(const float4*)(w + 4);
+    o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
+    o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
   }
 }
 
-template <typename TW, int PT, int NV>
-__global__ __launch_bounds__(256) void final_kernel(const float* __restrict__ x, ReqMap rm,
-                                                    const TW* __restrict__ w_out,
-                                                    const TW* __restrict__ b_out,
-                                                    const float* __restrict__ mod, int ld_mod,
-                                                    int shift_off, int scale_off, int D, int C,
-                                                    int p, float eps, float guidance,
-                                                    float* __restrict__ lat,
-                                                    float* __restrict__ noise_pred) {
-  constexpr int NI = NV ? (NV + 63) / 64 : kMaxV4;
-  // DiT width 1152, 16 outputs, bf16: the workgroup's four waves read the
-  // projection (36 KB) from LDS, staged once, instead of each from L2
-  constexpr bool WLDS = PT == 16 && NV == 288 && sizeof(TW) == 2;
-  __shared__ __attribute__((aligned(16))) TW wsh[WLDS ? 16 * 4 * 288 : 1];
-  if constexpr (WLDS) {
-    for (int i = threadIdx.x; i < 16 * 4 * 288 / 8; i += 256)
-      ((bf16x8*)wsh)[i] = ((const bf16x8*)w_out)[i];
-    __syncthreads();
-  }
-  const TW* wsrc = WLDS ? wsh : w_out;
-  const int lane = threadIdx.x & 63;
-  const int tok = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (tok >= rm.tokens_total) return;
-  const int r = req_of_token(rm, tok);
-  const int P = PT ? PT : p * p * C;
-  const int nv = NV ? NV : D >> 2;
-  const float* md = mod + (size_t)rm.modrow[r] * ld_mod;
-  const float4* sh = (const float4*)(md + shift_off);
-  const float4* sc = (const float4*)(md + scale_off);
-  const int nb = rm.branches;
-  float4 v[2][NI];
-  // LN-modulate both branches' rows in registers (static indices throughout,
-  // so that everything stays in registers)
-#pragma unroll
-  for (int br = 0; br < 2; ++br) {
-    if (br >= nb) continue;
-    const float4* xr = (const float4*)(x + ((size_t)br * rm.tokens_total + tok) * D);
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nv) {
-        v[br][i] = xr[c];
-        s += (v[br][i].x + v[br][i].y) + (v[br][i].z + v[br][i].w);
-      }
-    }
-    const float mean = wave_sum(s) / (float)D;
-    float q = 0.f;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nv) {
-        const float a = v[br][i].x - mean, b = v[br][i].y - mean, cc = v[br][i].z - mean,
-                    d = v[br][i].w - mean;
-        q += (a * a + b * b) + (cc * cc + d * d);
-      }
-    }
-    const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nv) {
-        const float4 a = sh[c], b = sc[c];
-        v[br][i].x = (v[br][i].x - mean) * rstd * (1.f + b.x) + a.x;
-        v[br][i].y = (v[br][i].y - mean) * rstd * (1.f + b.y) + a.y;
-        v[br][i].z = (v[br][i].z - mean) * rstd * (1.f + b.z) + a.z;
-        v[br][i].w = (v[br][i].w - mean) * rstd * (1.f + b.w) + a.w;
-      }
-    }
-  }
-  float mine[2] = {0.f, 0.f};
-  int f_own = lane;   // output this lane ends with
-  if constexpr (PT > 0) {
-    // per-lane partial sums of every output, then the reduce-scatter
-    float acc[2][PT];
-#pragma unroll
-    for (int f = 0; f < PT; ++f) acc[0][f] = acc[1][f] = 0.f;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nv) {
-#pragma unroll
-        for (int f = 0; f < PT; ++f) {
-          const float4 w = ld_w4<TW, PT>(wsrc + (size_t)f * D + 4 * c);
-#pragma unroll
-          for (int br = 0; br < 2; ++br) {
-            acc[br][f] = fmaf(v[br][i].x, w.x, acc[br][f]);
-            acc[br][f] = fmaf(v[br][i].y, w.y, acc[br][f]);
-            acc[br][f] = fmaf(v[br][i].z, w.z, acc[br][f]);
-            acc[br][f] = fmaf(v[br][i].w, w.w, acc[br][f]);
-          }
-        }
-      }
-    }
-    // step st (lane bit o = 32 >> st) halves the outputs a lane holds -- it
-    // keeps the half given by that bit -- until one is left, then plain
-    // butterfly steps
-    int base = 0;
-#pragma unroll
-    for (int st = 0; st < 6; ++st) {
-      const int o = 32 >> st;
-      const int K = PT >> st;          // outputs held before this step
-      const bool up = (lane & o) != 0;
-      if (K > 1) {
-        const int h = K / 2;
-#pragma unroll
-        for (int br = 0; br < 2; ++br)
-#pragma unroll
-          for (int t = 0; t < h; ++t) {
-            const float keep = up ? acc[br][t + h] : acc[br][t];
-            const float send = up ? acc[br][t] : acc[br][t + h];
-            acc[br][t] = keep + __shfl_xor(send, o, kWave);
-          }
-        if (up) base += h;
-      } else {
-#pragma unroll
-        for (int br = 0; br < 2; ++br) acc[br][0] += __shfl_xor(acc[br][0], o, kWave);
-      }
-    }
-    f_own = base;
-    const float bo = to_f32(b_out[f_own]);
-    mine[0] = acc[0][0] + bo;
-    mine[1] = acc[1][0] + bo;
-  } else {
-#pragma unroll
-    for (int br = 0; br < 2; ++br) {
-      if (br >= nb) continue;
-      for (int f = 0; f < P; ++f) {
-        const TW* wr = w_out + (size_t)f * D;
-        float part = 0.f;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-          const int c = lane + 64 * i;
-          if (c < nv) {
-            part = fmaf(v[br][i].x, to_f32(wr[4 * c + 0]), part);
-            part = fmaf(v[br][i].y, to_f32(wr[4 * c + 1]), part);
-            part = fmaf(v[br][i].z, to_f32(wr[4 * c + 2]), part);
-            part = fmaf(v[br][i].w, to_f32(wr[4 * c + 3]), part);
-          }
-        }
-        const float tot = wave_sum(part) + to_f32(b_out[f]);
-        if (lane == f) mine[br] = tot;
-      }
-    }
-  }
-  // one lane per output writes (for PT, the first of the lanes that hold it)
-  if (PT > 0 ? (lane & (64 / (PT > 0 ? PT : 64) - 1)) != 0 : lane >= P) return;
-  const float vel = nb == 2 ? mine[1] + guidance * (mine[0] - mine[1]) : mine[0];
-  const int f = f_own;
+// v = v_u + g (v_c - v_u) into output f of token `tok` (request r): unpatchify,
+// noise_pred, Euler update
+__device__ __forceinline__ void final_store(const ReqMap& rm, int tok, int r, int f, float vc,
+                                            float vu, float guidance, int C, int p, float* lat,
+                                            float* noise_pred) {
+  const float vel = rm.branches == 2 ? vu + guidance * (vc - vu) : vc;
   const int a = f / (p * C), b = (f / C) % p, c = f % C;
   const int lt = tok - rm.tok_off[r];
   const int W = rm.w[r], H = rm.h[r], gw = W / p;
@@ -950,140 +887,219 @@ __global__ __launch_bounds__(256) void final_kernel(const float* __restrict__ x,
   if (dt != 0.f) lat[li] = lat[li] + dt * vel;
 }
 
-// Final layer of the wide model (64 outputs of width 3072, bf16 weights):
-// a workgroup takes kFwTok tokens so that each 64-column chunk of the
-// projection, staged in LDS as fp32, serves all of them (the per-token wave
-// above reads the 384 KB projection from L2 once per token).  Per guidance
-// branch: the tokens' LayerNorm statistics (two passes over each row, one
-// wave per token), then for each 64-column chunk the modulated rows and the
-// projection's columns go to LDS and every thread accumulates 4 tokens x 2
-// outputs in fp32, K ascending; then guidance, unpatchify, noise_pred and
-// the Euler update as in final_kernel.
-constexpr int kFwTok = 32, kFwK = 64, kFwP = 64;
-
-__global__ __launch_bounds__(256) void final_wide_kernel(const float* __restrict__ x, ReqMap rm,
-                                                         const bf16* __restrict__ w_out,
-                                                         const bf16* __restrict__ b_out,
+// NT: P / 16; NI: float4 per lane and row (D <= 256 NI); CH: columns in LDS at
+// a time (a multiple of 256, or all of them)
+template <typename TW, int NT, int NI, int CH, int NB>
+__global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict__ x, ReqMap rm,
+                                                         const TW* __restrict__ w_out,
+                                                         const TW* __restrict__ b_out,
                                                          const float* __restrict__ mod, int ld_mod,
                                                          int shift_off, int scale_off, int D, int C,
                                                          int p, float eps, float guidance,
                                                          float* __restrict__ lat,
                                                          float* __restrict__ noise_pred) {
-  __shared__ float hs[kFwTok][kFwK + 1];
-  __shared__ float ws[kFwP][kFwK + 1];
-  __shared__ float st_mean[kFwTok], st_rstd[kFwTok];
-  __shared__ int st_row[kFwTok];   // modulation row of each token (-1 past the end)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int tok0 = blockIdx.x * kFwTok;
-  const int T = rm.tokens_total, nb = rm.branches;
-  const int ty = tid >> 5, tx = tid & 31;   // tokens 4 ty .. +3, outputs 2 tx, 2 tx + 1
-  if (tid < kFwTok) {
-    const int t = tok0 + tid;
-    st_row[tid] = t < T ? rm.modrow[req_of_token(rm, t)] : -1;
+  constexpr int NR = 2 * NB, P = CH + 4;   // rows per wave; LDS row pitch
+  constexpr int ROWS = NB * 16 * P * 4, PART = 8 * NB * NT * 64 * 16;
+  __shared__ __attribute__((aligned(16))) char smem[ROWS > PART ? ROWS : PART];
+  float* const hs = (float*)smem;          // [NB][16][P]
+  f32x4* const part = (f32x4*)smem;        // [wave][NB][NT][64], after the last columns
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 15, g = lane >> 4;
+  const int T = rm.tokens_total, tok0 = blockIdx.x * 16;
+  const int nv = D >> 2;
+  // rows: branch i / 2, token 2 wave + i % 2 of the group (past the end: the last token)
+  float4 v[NR][NI];
+  float mean[NR], rstd[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int t = min(tok0 + 2 * wave + (i & 1), T - 1);
+    const float4* xr = (const float4*)(x + ((size_t)(i >> 1) * T + t) * D);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int c = lane + 64 * j;
+      v[i][j] = float4{0.f, 0.f, 0.f, 0.f};
+      if (c < nv) v[i][j] = xr[c];
+    }
   }
-  float res[2][4][2];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    float s = 0.f, q = 0.f;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) s += (v[i][j].x + v[i][j].y) + (v[i][j].z + v[i][j].w);
+    mean[i] = wave_sum_dpp(s) / (float)D;
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+      if (lane + 64 * j < nv) {
+        const float a = v[i][j].x - mean[i], b = v[i][j].y - mean[i], c = v[i][j].z - mean[i],
+                    d = v[i][j].w - mean[i];
+        q += (a * a + b * b) + (c * c + d * d);
+      }
+    rstd[i] = 1.0f / sqrtf(wave_sum_dpp(q) / (float)D + eps);
+  }
+  // the modulation rows of the wave's two tokens
+  const float* md[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    md[i] = mod + (size_t)rm.modrow[req_of_token(rm, min(tok0 + 2 * wave + i, T - 1))] * ld_mod;
+
+  f32x4 acc[NB][NT];
+#pragma unroll
+  for (int br = 0; br < NB; ++br)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[br][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int NCH = CH % 256 ? 1 : NI * 256 / CH;   // (whole rows when CH is no multiple of 256)
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) {
+    const int k0 = ch * CH;
+    if (k0 >= D) break;
+    if (ch > 0) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      // (with several chunks CH is a multiple of 256: a float4 column lies in one)
+      if (NCH > 1 && j / (CH / 256) != ch) continue;
+      const int c = lane + 64 * j;
+      if (c < nv) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const float4 a = *(const float4*)(md[t] + shift_off + 4 * c);
+          const float4 b = *(const float4*)(md[t] + scale_off + 4 * c);
+#pragma unroll
+          for (int br = 0; br < NB; ++br) {
+            const int i = 2 * br + t;
+            float4 y;
+            y.x = (v[i][j].x - mean[i]) * rstd[i] * (1.f + b.x) + a.x;
+            y.y = (v[i][j].y - mean[i]) * rstd[i] * (1.f + b.y) + a.y;
+            y.z = (v[i][j].z - mean[i]) * rstd[i] * (1.f + b.z) + a.z;
+            y.w = (v[i][j].w - mean[i]) * rstd[i] * (1.f + b.w) + a.w;
+            *(float4*)&hs[(br * 16 + 2 * wave + t) * P + 4 * c - k0] = y;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    const int kn = min(CH, D - k0);
+#pragma unroll 2
+    for (int k = 32 * wave + 8 * g; k < kn; k += 256) {
+      float w[NT][8];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) ld_w8(w_out + (size_t)(16 * j + fr) * D + k0 + k, w[j]);
+#pragma unroll
+      for (int br = 0; br < NB; ++br) {
+        float h[8];
+        ld_w8((const float*)&hs[(br * 16 + fr) * P + k], h);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+            acc[br][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][e], h[e], acc[br][j], 0, 0, 0);
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int br = 0; br < NB; ++br)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) part[((wave * NB + br) * NT + j) * 64 + lane] = acc[br][j];
+  __syncthreads();
+  // lane: token fr, outputs 16 j + 4 g .. + 3
+  const int tok = tok0 + fr;
+  if (tok >= T) return;
+  const int r = req_of_token(rm, tok);
+  for (int j = wave; j < NT; j += 8) {
+    f32x4 y[2];
+    y[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int br = 0; br < NB; ++br) {
+      y[br] = part[(br * NT + j) * 64 + lane];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) y[br] += part[((q * NB + br) * NT + j) * 64 + lane];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int f = 16 * j + 4 * g + e;
+      const float bo = to_f32(b_out[f]);
+      final_store(rm, tok, r, f, y[0][e] + bo, y[1][e] + bo, guidance, C, p, lat, noise_pred);
+    }
+  }
+}
+
+// Any other P (<= 64): one wave per token, each output summed over the wave.
+template <typename TW>
+__global__ __launch_bounds__(256) void final_kernel(const float* __restrict__ x, ReqMap rm,
+                                                    const TW* __restrict__ w_out,
+                                                    const TW* __restrict__ b_out,
+                                                    const float* __restrict__ mod, int ld_mod,
+                                                    int shift_off, int scale_off, int D, int C,
+                                                    int p, float eps, float guidance,
+                                                    float* __restrict__ lat,
+                                                    float* __restrict__ noise_pred) {
+  constexpr int NI = kMaxV4;
+  const int lane = threadIdx.x & 63;
+  const int tok = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (tok >= rm.tokens_total) return;
+  const int r = req_of_token(rm, tok);
+  const int P = p * p * C;
+  const int nv = D >> 2;
+  const float* md = mod + (size_t)rm.modrow[r] * ld_mod;
+  const float4* sh = (const float4*)(md + shift_off);
+  const float4* sc = (const float4*)(md + scale_off);
+  const int nb = rm.branches;
+  float mine[2] = {0.f, 0.f};
 #pragma unroll
   for (int br = 0; br < 2; ++br) {
-    if (br >= nb) break;
-    __syncthreads();
-    // statistics: wave w takes tokens w, w + 4, ...
-    for (int i = wave; i < kFwTok; i += 4) {
-      const int t = tok0 + i;
-      float mean = 0.f, rstd = 0.f;
-      if (t < T) {
-        const float4* xr = (const float4*)(x + ((size_t)br * T + t) * D);
-        float s = 0.f;
-        for (int c = lane; c < D / 4; c += 64) {
-          const float4 v = xr[c];
-          s += (v.x + v.y) + (v.z + v.w);
-        }
-        mean = wave_sum(s) / (float)D;
-        float q = 0.f;
-        for (int c = lane; c < D / 4; c += 64) {
-          const float4 v = xr[c];
-          const float a = v.x - mean, b = v.y - mean, cc = v.z - mean, d = v.w - mean;
-          q += (a * a + b * b) + (cc * cc + d * d);
-        }
-        rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
-      }
-      if (lane == 0) {
-        st_mean[i] = mean;
-        st_rstd[i] = rstd;
+    if (br >= nb) continue;
+    float4 v[NI];
+    const float4* xr = (const float4*)(x + ((size_t)br * rm.tokens_total + tok) * D);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int c = lane + 64 * i;
+      if (c < nv) {
+        v[i] = xr[c];
+        s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
       }
     }
-    float acc[4][2] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
-    for (int k0 = 0; k0 < D; k0 += kFwK) {
-      __syncthreads();
-      // modulated rows: 32 tokens x 64 columns, 8 per thread (2 float4)
+    const float mean = wave_sum(s) / (float)D;
+    float q = 0.f;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int e = tid + 256 * j, t = e >> 4, c4 = (e & 15) * 4;
-        float4 h = float4{0.f, 0.f, 0.f, 0.f};
-        const int mr = st_row[t];
-        if (mr >= 0) {
-          const float4 v = *(const float4*)(x + ((size_t)br * T + tok0 + t) * D + k0 + c4);
-          const float* md = mod + (size_t)mr * ld_mod;
-          const float4 sh = *(const float4*)(md + shift_off + k0 + c4);
-          const float4 sc = *(const float4*)(md + scale_off + k0 + c4);
-          const float mu = st_mean[t], rs = st_rstd[t];
-          h.x = (v.x - mu) * rs * (1.f + sc.x) + sh.x;
-          h.y = (v.y - mu) * rs * (1.f + sc.y) + sh.y;
-          h.z = (v.z - mu) * rs * (1.f + sc.z) + sh.z;
-          h.w = (v.w - mu) * rs * (1.f + sc.w) + sh.w;
-        }
-        hs[t][c4] = h.x;
-        hs[t][c4 + 1] = h.y;
-        hs[t][c4 + 2] = h.z;
-        hs[t][c4 + 3] = h.w;
-      }
-      // the projection's 64 x 64 chunk, 16 per thread (2 x 8 bf16)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int e = tid + 256 * j, f = e >> 3, c8 = (e & 7) * 8;
-        const bf16x8 w = *(const bf16x8*)(w_out + (size_t)f * D + k0 + c8);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) ws[f][c8 + q] = (float)w[q];
-      }
-      __syncthreads();
-#pragma unroll 8
-      for (int k = 0; k < kFwK; ++k) {
-        const float w0 = ws[2 * tx][k], w1 = ws[2 * tx + 1][k];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float h = hs[4 * ty + i][k];
-          acc[i][0] = fmaf(h, w0, acc[i][0]);
-          acc[i][1] = fmaf(h, w1, acc[i][1]);
-        }
+    for (int i = 0; i < NI; ++i) {
+      const int c = lane + 64 * i;
+      if (c < nv) {
+        const float a = v[i].x - mean, b = v[i].y - mean, cc = v[i].z - mean, d = v[i].w - mean;
+        q += (a * a + b * b) + (cc * cc + d * d);
       }
     }
+    const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      res[br][i][0] = acc[i][0];
-      res[br][i][1] = acc[i][1];
+    for (int i = 0; i < NI; ++i) {
+      const int c = lane + 64 * i;
+      if (c < nv) {
+        const float4 a = sh[c], b = sc[c];
+        v[i].x = (v[i].x - mean) * rstd * (1.f + b.x) + a.x;
+        v[i].y = (v[i].y - mean) * rstd * (1.f + b.y) + a.y;
+        v[i].z = (v[i].z - mean) * rstd * (1.f + b.z) + a.z;
+        v[i].w = (v[i].w - mean) * rstd * (1.f + b.w) + a.w;
+      }
+    }
+    for (int f = 0; f < P; ++f) {
+      const TW* wr = w_out + (size_t)f * D;
+      float part = 0.f;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int c = lane + 64 * i;
+        if (c < nv) {
+          part = fmaf(v[i].x, to_f32(wr[4 * c + 0]), part);
+          part = fmaf(v[i].y, to_f32(wr[4 * c + 1]), part);
+          part = fmaf(v[i].z, to_f32(wr[4 * c + 2]), part);
+          part = fmaf(v[i].w, to_f32(wr[4 * c + 3]), part);
+        }
+      }
+      const float tot = wave_sum(part) + to_f32(b_out[f]);
+      if (lane == f) mine[br] = tot;
     }
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int tok = tok0 + 4 * ty + i;
-    if (tok >= T) continue;
-    const int r = req_of_token(rm, tok);
-    const int lt = tok - rm.tok_off[r];
-    const int W = rm.w[r], H = rm.h[r], gw = W / p;
-    const int gi = lt / gw, gj = lt - gi * gw;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int f = 2 * tx + j;
-      const float bo = (float)b_out[f];
-      const float vc = res[0][i][j] + bo;
-      const float vel = nb == 2 ? (res[1][i][j] + bo) + guidance * (vc - (res[1][i][j] + bo)) : vc;
-      const int a = f / (p * C), b = (f / C) % p, c = f % C;
-      const size_t li =
-          (size_t)rm.lat_off[r] + (size_t)c * H * W + (size_t)(gi * p + a) * W + gj * p + b;
-      if (noise_pred) noise_pred[li] = vel;
-      const float dt = rm.dt[r];
-      if (dt != 0.f) lat[li] = lat[li] + dt * vel;
-    }
-  }
+  if (lane < P) final_store(rm, tok, r, lane, mine[0], mine[1], guidance, C, p, lat, noise_pred);
 }
 
 hipError_t launch_final_layer(const float* x, const ReqMap& rm, const void* w_out,
@@ -1091,26 +1107,35 @@ hipError_t launch_final_layer(const float* x, const ReqMap& rm, const void* w_ou
                               int shift_off, int scale_off, int D, int C, int p, float eps,
                               float guidance, float* latents, float* noise_pred, hipStream_t st) {
   if (rm.tokens_total == 0) return hipSuccess;
-  dim3 grid((rm.tokens_total + 3) / 4), block(256);
-  const int P = p * p * C;
-#define T2I_FIN(TW_, PT_, NV_)                                                                 \
-  hipLaunchKernelGGL((final_kernel<TW_, PT_, NV_>), grid, block, 0, st, x, rm, (const TW_*)w_out, \
+  const int P = p * p * C, T = rm.tokens_total;
+#define T2I_FIN(K_, GRID_, BLOCK_, TW_)                                                          \
+  hipLaunchKernelGGL(K_, dim3(GRID_), dim3(BLOCK_), 0, st, x, rm, (const TW_*)w_out,             \
                      (const TW_*)b_out, mod, ld_mod, shift_off, scale_off, D, C, p, eps, guidance, \
                      latents, noise_pred)
-  if (w_bf16) {
-    if (P == 16 && D == 1152) T2I_FIN(bf16, 16, 288);
-    else if (P == kFwP && D % kFwK == 0 && (uintptr_t)w_out % 16 == 0) {
-      hipLaunchKernelGGL(final_wide_kernel, dim3((rm.tokens_total + kFwTok - 1) / kFwTok), block,
-                         0, st, x, rm, (const bf16*)w_out, (const bf16*)b_out, mod, ld_mod,
-                         shift_off, scale_off, D, C, p, eps, guidance, latents, noise_pred);
-      return hipGetLastError();
-    }
-    else if (P == 16) T2I_FIN(bf16, 16, 0);
-    else T2I_FIN(bf16, 0, 0);
-  } else {
-    if (P == 16) T2I_FIN(float, 16, 0);
-    else T2I_FIN(float, 0, 0);
+  // (16-byte weight loads)
+  const bool al = (uintptr_t)w_out % 16 == 0, two = rm.branches == 2;
+  const int gt = (T + 15) / 16;
+#define T2I_FIN_NB(TW_, NT_, NI_, CH_)                                                           \
+  if (two) T2I_FIN((final_mfma_kernel<TW_, NT_, NI_, CH_, 2>), gt, 512, TW_);                    \
+  else T2I_FIN((final_mfma_kernel<TW_, NT_, NI_, CH_, 1>), gt, 512, TW_)
+  // rows of at most 1152 columns are staged whole, wider ones 1024 at a time
+#define T2I_FIN_MF(TW_)                                                                          \
+  if (P == 16 && D <= 1152 && al) {                                                              \
+    T2I_FIN_NB(TW_, 1, 5, 1152);                                                                 \
+  } else if (P == 16 && al) {                                                                    \
+    T2I_FIN_NB(TW_, 1, kMaxV4, 1024);                                                            \
+  } else if (P == 64 && al) {                                                                    \
+    T2I_FIN_NB(TW_, 4, kMaxV4, 1024);                                                            \
+  } else {                                                                                       \
+    T2I_FIN((final_kernel<TW_>), (T + 3) / 4, 256, TW_);                                         \
   }
+  if (w_bf16) {
+    T2I_FIN_MF(bf16);
+  } else {
+    T2I_FIN_MF(float);
+  }
+#undef T2I_FIN_MF
+#undef T2I_FIN_NB
 #undef T2I_FIN
   return hipGetLastError();
 }

@@ -215,10 +215,10 @@ bool gemm_bf16_groupable(int M, int N, int kind);
 hipError_t launch_gemm_bf16_group(const bf16* A, int lda, const PtrGroup& g, int groups, int ldw,
                                   int M, int N, int K, int kind, const Epi& epi, hipStream_t st);
 // Grouped conditioning GEMV (EPI_STORE), bitwise the per-group
-// launch_linear_rows results.
+// launch_linear_rows results; the last group has n_last <= N columns.
 hipError_t launch_linear_rows_group(const float* A, int lda, const PtrGroup& g, int groups,
-                                    int ldw, bool w_bf16, int M, int N, int K, const Epi& epi,
-                                    hipStream_t st);
+                                    int ldw, bool w_bf16, int M, int N, int n_last, int K,
+                                    const Epi& epi, hipStream_t st);
 hipError_t launch_linear_rows(const float* A, int lda, const void* W, int ldw, bool w_bf16,
                               const void* bias, int M, int N, int K, int kind, const Epi& epi,
                               hipStream_t st);
@@ -251,15 +251,17 @@ hipError_t launch_ln_modulate(bool bf16_out, int rows, int D, const float* x, in
                               const float* mod, int ld_mod, int shift_off, int scale_off,
                               const SeqMap& map, void* out, int ldo, float eps, hipStream_t st);
 
-// pe_table: workspace for the 2D sin-cos table (pe_npos x D/4 float2), NULL
-// for no position embedding; pe_npos = largest grid side of the call
+// pe_table: the call's 2D sin-cos table (launch_call_tables), NULL for no
+// position embedding; x0 NULL where only the `copies` copies in x are wanted
 hipError_t launch_embed(const float* lat, const ReqMap& rm, const void* w_pe, const void* b_pe,
-                        bool w_bf16, int D, int C, int p, float2* pe_table, int pe_npos,
-                        float* x0, float* x, int copies, hipStream_t st);
+                        bool w_bf16, int D, int C, int p, const float2* pe_table, float* x0,
+                        float* x, int copies, hipStream_t st);
 
-// t: HOST array of `rows` timesteps (launched in chunks of kTValsChunk).
-hipError_t launch_timestep_freq(const double* t, int rows, int freq_dim, double t_scale,
-                                float* out, hipStream_t st);
+// The tables that depend on the call's arguments only: the sinusoids of `rows`
+// timesteps (t: HOST array, launched in chunks of kTValsChunk) into out, and
+// the position table tab [npos][q] (see the kernel).
+hipError_t launch_call_tables(const double* t, int rows, int freq_dim, double t_scale, float* out,
+                              float2* tab, int npos, int q, bool cos_first, hipStream_t st);
 
 hipError_t launch_broadcast_rows(const void* src, bool bf16_io, int rows, int D, void* dst,
                                  hipStream_t st);
@@ -269,12 +271,11 @@ hipError_t launch_final_layer(const float* x, const ReqMap& rm, const void* w_ou
                               int shift_off, int scale_off, int D, int C, int p, float eps,
                               float guidance, float* latents, float* noise_pred, hipStream_t st);
 
-// 2D RoPE.  table[pos * q + j] = (cos, sin)(pos * 10000^(-j/q)), q = head_dim/4,
-// pos < npos; rope_apply rotates, in place, the q (columns [0, D)) and k
+// 2D RoPE.  table[pos * q + j] = (cos, sin)(pos * 10000^(-j/q)), q = head_dim/4;
+// rope_apply rotates, in place, the q (columns [0, D)) and k
 // (columns [D, 2D)) of the image rows [row0, row0 + branches * tokens) of a
 // bf16 buffer with row stride ld: the first head_dim/2 dims of each head by
 // the token's grid row, the last head_dim/2 by its grid column, pairs (2j, 2j+1).
-hipError_t launch_rope_table(float2* table, int npos, int q, hipStream_t st);
 hipError_t launch_rope_apply(bf16* qk, int ld, int row0, const ReqMap& rm, int heads, int head_dim,
                              int patch, const float2* table, hipStream_t st);
 // W <- W + alpha B A (LoRA merge), W [n_out, n_in] stride ldw, rank <= 128
