@@ -33,7 +33,8 @@ hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const
                            hipStream_t st);
 hipError_t launch_gemm_dma_small(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
                                  int M, int N, int K, int kind, const Epi& epi, int vec_ok,
-                                 hipStream_t st);
+                                 hipStream_t st, int splits = 1);
+bool gemm_dma_small_fits(int M, int N);
 
 // Map launch order -> tile order so XCD x (blocks b with b % 8 == x) owns the
 // contiguous tile range of its share.
@@ -458,10 +459,11 @@ hipError_t launch_gemm_bf16(const bf16* A, int lda, const bf16* W, int ldw, cons
   // chip (e.g. the 512-row text stream against K = 3072 or 12288).
   // (the direct-load kernels address each operand with 32-bit byte offsets)
   const bool dma_fits = (size_t)2 * M * lda < 0x7fffffff && (size_t)2 * N * ldw < 0x7fffffff;
-  if (M >= 2048 && (N % 144 == 0 || N % 128 == 0) && kind != EPI_SILU && dma_fits)
+  if (M >= 2048 && (N % 144 == 0 || N % 128 == 0) && dma_fits)
     return launch_gemm_dma(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
   const int splits = splitk_ws ? splitk_factor(N, K) : 1;
-  if (splits == 1 && N % 144 == 0 && K % 64 == 0 && kind != EPI_SILU && dma_fits && M >= 64)
+  const bool small_dma = dma_fits && K % 64 == 0 && gemm_dma_small_fits(M, N);
+  if (splits == 1 && small_dma)
     return launch_gemm_dma_small(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
   if (splits > 1 && (size_t)splits * M * N <= splitk_floats && kind != EPI_SILU) {
     Epi pe;
@@ -469,17 +471,15 @@ hipError_t launch_gemm_bf16(const bf16* A, int lda, const bf16* W, int ldw, cons
     pe.out = splitk_ws;
     pe.ldo = N;
     const int pvec = N % 4 == 0;
-    // 64 x 64 tiles where 128-row tiles would leave most CUs idle (the
-    // caption projection of one request: 120 rows); same K order, same sums
-    const long t128 = (long)((M + 127) / 128) * ((N + (N % 144 == 0 ? 143 : 127)) /
-                                                  (N % 144 == 0 ? 144 : 128));
+    // 64 x 64 register-staged tiles where 128-row tiles would leave most CUs
+    // idle; same K order, same sums
+    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     hipError_t err =
-        t128 * splits < 256
+        small_dma ? launch_gemm_dma_small(A, lda, W, ldw, bias, M, N, K / splits, EPI_PARTIAL, pe,
+                                          pvec, st, splits)
+        : t128 * splits < 256
             ? gemm_bf16_dispatch<64, 64, 2>(A, lda, W, ldw, bias, M, N, K / splits, EPI_PARTIAL,
                                             pe, pvec, st, splits)
-        : N % 144 == 0
-            ? gemm_bf16_dispatch<128, 144, 4>(A, lda, W, ldw, bias, M, N, K / splits, EPI_PARTIAL,
-                                              pe, pvec, st, splits)
             : gemm_bf16_dispatch<128, 128, 2>(A, lda, W, ldw, bias, M, N, K / splits, EPI_PARTIAL,
                                               pe, pvec, st, splits);
     if (err != hipSuccess) return err;

@@ -140,9 +140,17 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   constexpr int BPW = (TBLK + NW - 1) / NW;                       // load instructions per wave
   constexpr int STAGE = (BM + BN) * 64;                            // bf16 elements per stage
   constexpr bool CT = KIND != EPI_SPLIT_VT;
+  // split-K: workgroup row blockIdx.y takes K columns [y K, (y + 1) K) and
+  // writes its partial sums (no bias) to slice y of the fp32 output
+  constexpr bool PART = KIND == EPI_PARTIAL;
+  constexpr int EK = PART ? EPI_STORE_F32 : KIND;
+  if constexpr (PART) {
+    A += (size_t)blockIdx.y * K;
+    W += (size_t)blockIdx.y * K;
+    epi.out = (float*)epi.out + (size_t)blockIdx.y * M * epi.ldo;
+  }
   static_assert(BM % 8 == 0 && BN % 8 == 0 && WM % 16 == 0 && WN % 16 == 0, "tile shape");
   static_assert(ST >= 2 && ST <= 7 && (ST - 2) * BPW < 64, "stages");
-  static_assert(ABLK % NW == 0, "A / W blocks split evenly over the load rounds");
   // the stage ring, then the epilogue's fp32 bias and gate rows (one LDS
   // object: with several, the compiler makes every fragment read wait for
   // all outstanding tile loads)
@@ -151,7 +159,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   float* const ebias = (float*)(smem + ST * STAGE);
   float* const egate = ebias + BN;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   // tile order: the tiles of one XCD are consecutive; within that range they
   // walk group_m row blocks down before moving one column block right, so the
@@ -164,29 +173,46 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   const int m0 = (first + in_grp % rows_in) * BM, n0 = (in_grp / rows_in) * BN;
 
   // this lane's byte offset of every block it loads, from A or W (the k
-  // position is added per tile as the scalar offset); load round i reads A
-  // while i < ABLK / NW
-  uint32_t src[BPW];
+  // position is added per tile as the scalar offset); load round i takes block
+  // wave + i NW: of A while that is below ABLK (a round may hold both)
+  // (256-row tiles are launched with whole column tiles only: their W rows are
+  // uniform steps from the first one, which go into the scalar offset)
+  constexpr int ARND = ABLK / NW;
+  constexpr bool NWHOLE = BM == 256 && ABLK % NW == 0;
+  uint32_t src[NWHOLE ? ARND + 1 : BPW];
   int dst[BPW];   // byte offset of the block inside a stage (wave-uniform)
 #pragma unroll
   for (int i = 0; i < BPW; ++i) {
     int b = wave + i * NW;
     if (b >= TBLK) b -= NW;               // repeat this wave's previous block
-    const int lr = (b < ABLK ? b : b - ABLK) * 8 + (lane >> 3);   // row within A or W tile
-    const int c = (lane & 7) ^ ((lr >> 1) & 7);                   // logical chunk of this slot
-    src[i] = 2u * (uint32_t)(i < ABLK / NW ? min(m0 + lr, M - 1) * lda + c * 8
-                                           : min(n0 + lr, N - 1) * ldw + c * 8);
     dst[i] = b * 1024;
+    if (NWHOLE && i > ARND) continue;
+    const bool is_a = b < ABLK;
+    const int lr = (is_a ? b : b - ABLK) * 8 + (lane >> 3);       // row within A or W tile
+    const int c = (lane & 7) ^ ((lr >> 1) & 7);                   // logical chunk of this slot
+    src[i] = 2u * (uint32_t)(is_a ? min(m0 + lr, M - 1) * lda + c * 8
+                                  : min(n0 + lr, N - 1) * ldw + c * 8);
   }
   const __amdgpu_buffer_rsrc_t ra =
       __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, 0x7fffffff, 0x00020000);
   const __amdgpu_buffer_rsrc_t rw =
       __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, 0x7fffffff, 0x00020000);
-  auto issue = [&](int t, int stage) {
+  // the round that holds blocks of both operands, this wave's
+  const __amdgpu_buffer_rsrc_t rmix = __builtin_amdgcn_make_buffer_rsrc(
+      wave + ARND * NW < ABLK ? (void*)A : (void*)W, 0, 0x7fffffff, 0x00020000);
+  // load i of K step t into the slot at byte offset `slot`
+  auto issue1 = [&](int i, int t, uint32_t slot) {
     const int kb = t * 128;   // byte offset of the tile's 64 k values
+    if (NWHOLE && i > ARND)
+      dma16<AUX>(rw, (char*)smem + slot + dst[i], src[ARND],
+                 kb + (dst[i] - dst[ARND]) / 1024 * 16 * ldw);
+    else
+      dma16<AUX>(i < ARND ? ra : i == ARND && ABLK % NW ? rmix : rw, (char*)smem + slot + dst[i],
+                 src[NWHOLE ? min(i, ARND) : i], kb);
+  };
+  auto issue = [&](int t, int stage) {
 #pragma unroll
-    for (int i = 0; i < BPW; ++i)
-      dma16<AUX>(i < ABLK / NW ? ra : rw, (char*)smem + stage * STAGE * 2 + dst[i], src[i], kb);
+    for (int i = 0; i < BPW; ++i) issue1(i, t, stage * STAGE * 2);
   };
 
   f32x4 acc[TM][TN];
@@ -225,7 +251,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   // load (so the vmcnt thresholds below, which count younger loads, stay
   // exact), and put them in LDS after the main loop; the epilogue then reads
   // LDS only and its stores never wait behind a global load.
-  const bool whole_n = vec_ok && n0 + BN <= N;
+  const bool whole_n = !PART && vec_ok && n0 + BN <= N;
   bool one_seq = false;
   int grow = 0;
   if constexpr (GATED) {
@@ -248,7 +274,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   // faster for the gated updates -- out-projection 45.5 -> 40.2 us, fc2 --
   // and, once the epilogue read its bias from LDS, for the plain one after
   // cross-attention too: 37.8 -> 35.5 us.)
-  constexpr bool PREX = CT && (KIND == EPI_RESID_GATED || KIND == EPI_RESID) && TM * TN <= 18;
+  // (where the wave's registers, 512 shared by the waves of a SIMD, hold both)
+  constexpr int BUDGET = 512 / ((NW + 3) / 4);
+  constexpr bool PREX = CT && (KIND == EPI_RESID_GATED || KIND == EPI_RESID) && TM * TN <= 18 &&
+                        2 * TM * TN * 4 + (TM + TN) * 4 + 40 <= BUDGET;
   float4 xpre[PREX ? TM : 1][PREX ? TN : 1];
   if constexpr (PREX) {
 #pragma unroll
@@ -315,7 +344,91 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   // loop.
   constexpr int REGS = TM * TN * 4 + 2 * (TM + TN) * 4 + (PREX ? TM * TN * 4 : 0);
   constexpr bool HALF_STEP = ST >= 3 && BM < 256 && REGS <= 176;
-  if constexpr (HALF_STEP) {
+  constexpr bool ROLL = BM == 256 && BN != 144 && BN != 288 && NW == 8;
+  if constexpr (ROLL) {
+    // this lane's byte offset in a 16-row fragment (the swizzle depends on the
+    // row within it alone); half-step 1 flips bit 6
+    const uint32_t fo = fr * 128 + ((g ^ ((fr >> 1) & 7)) << 4);
+    const uint32_t wao = wm * (WM * 128), wbo = (BM + wn * WN) * 128;
+    auto rd = [&](uint32_t base, int i) {
+      return *(const bf16x8*)((const char*)smem + base + i * 2048);
+    };
+    bf16x8 a0[TM], a1[TM], b[TN];
+    auto column = [&](int j, const bf16x8 (&a)[TM]) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        acc[i][j] = CT ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    };
+    constexpr int S = TN / 3;                                // columns before the barrier
+    constexpr int LPC = (BPW + TN - S - 1) / (TN - S);       // tile loads per column after it
+    // half-step 0 of the stage at byte offset so, reading half-step 1's
+    // fragments as it goes, and the first S columns of half-step 1
+    auto half0 = [&](uint32_t so) {
+      uint32_t ao = (fo ^ 64u) + (so + wao), bo = (fo ^ 64u) + (so + wbo);
+      asm volatile("" : "+v"(ao), "+v"(bo));   // (each read one of these plus an immediate)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a1[i] = rd(ao, i);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        column(j, a0);
+        b[j] = rd(bo, j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int j = 0; j < S; ++j) column(j, a1);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s)
+      if (s < KT) issue(s, s);
+    wait_rounds<BPW>(min(ST - 2, KT - 1));
+    block_barrier();
+    if (ST - 1 < KT) issue(ST - 1, ST - 1);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) a0[i] = rd(fo + wao, i);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) b[j] = rd(fo + wbo, j);
+    uint32_t so = 0;   // byte offset of stage t's slot
+    // (one rolled loop with one exit: with the slots unrolled the accumulators
+    // get a register set per exit)
+#pragma unroll 1
+    for (int t = 0; t < KT - 1; ++t) {
+      half0(so);
+      // stage t + 1 landed
+      if (ST == 2 || t + 2 >= KT) wait_vmcnt<0>();
+      else if (ST == 3 || t + 3 >= KT) wait_vmcnt<BPW>();
+      else wait_rounds<BPW>(min(ST - 2, KT - 2 - t));
+      block_barrier();
+      const uint32_t sn = so == (ST - 1) * STAGE * 2 ? 0 : so + STAGE * 2;
+      uint32_t ao = fo + (sn + wao), bo = fo + (sn + wbo);
+      asm volatile("" : "+v"(ao), "+v"(bo));
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a0[i] = rd(ao, i);
+#pragma unroll
+      for (int j = 0; j < S; ++j) b[j] = rd(bo, j);
+      const bool more = t + ST < KT;
+      if (XT::on && t + 2 == KT) xattn_prefetch();
+#pragma unroll
+      for (int j = S; j < TN; ++j) {
+        column(j, a1);
+        b[j] = rd(bo, j);
+        if (more) {
+#pragma unroll
+          for (int q = 0; q < LPC; ++q) {
+            const int i = (j - S) * LPC + q;
+            if (i < BPW) issue1(i, t + ST, so);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      so = sn;
+    }
+    if (XT::on && KT == 1) xattn_prefetch();
+    half0(so);
+#pragma unroll
+    for (int j = S; j < TN; ++j) column(j, a1);
+  } else if constexpr (HALF_STEP) {
     auto read_frags = [&](int slot, int kk, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
       const bf16* sA = smem + slot * STAGE;
       const bf16* sB = sA + BM * 64;
@@ -458,7 +571,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
     // (out-projection 41.0 -> 39.6 us at 8192 rows, 73.5 -> 62.0 at 12 032)
     // except 256 x 256 (the joint-attention model's fc1 measured 2.8 %
     // slower), not for the small-M tiles (no gain at 1024 rows).
-    constexpr bool STAGED = BM == 256 && BN != 256 && KIND != EPI_STORE_F32 && KIND != EPI_SILU;
+    constexpr bool STAGED = BM == 256 && BN != 256 && KIND != EPI_STORE_F32 && !PART;
     // (16-byte row chunks: row strides and bases must keep them aligned)
     constexpr bool F32O = KIND == EPI_RESID || KIND == EPI_RESID_GATED;
     const bool aligned16 =
@@ -518,6 +631,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
             for (int r = 0; r < 4; ++r) {
               float y = v[r];
               if (KIND == EPI_GELU) y = gelu_tanh(y);
+              if (KIND == EPI_SILU) y = silu(y);
               if (KIND == EPI_STORE) y *= qs;
               w[r] = (bf16)y;
             }
@@ -564,15 +678,16 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
         for (int j = 0; j < TN; ++j) {
           const int nb = n0 + wn * WN + j * 16 + g * 4;
           if (vec_ok && nb + 3 < N) {
-            const bf16x4 b4 = *(const bf16x4*)(bias + nb);
+            const bf16x4 b4 = PART ? bf16x4{} : *(const bf16x4*)(bias + nb);
             const float v[4] = {acc[i][j][0] + (float)b4[0], acc[i][j][1] + (float)b4[1],
                                 acc[i][j][2] + (float)b4[2], acc[i][j][3] + (float)b4[3]};
-            if constexpr (PREX) dma_epi4<KIND>(epi, m, nb, v, &xpre[i][j]);
-            else dma_epi4<KIND>(epi, m, nb, v);
+            if constexpr (PREX) dma_epi4<EK>(epi, m, nb, v, &xpre[i][j]);
+            else dma_epi4<EK>(epi, m, nb, v);
           } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-              if (nb + r < N) epi_apply<bf16>(epi, KIND, m, nb + r, acc[i][j][r] + (float)bias[nb + r]);
+              if (nb + r < N)
+                epi_apply<bf16>(epi, EK, m, nb + r, acc[i][j][r] + (PART ? 0.f : (float)bias[nb + r]));
           }
         }
       }
@@ -845,9 +960,9 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_vt_pipe_kernel(
 template <int BM, int BN, int WGM, int WGN, int ST, int AUX>
 hipError_t gemm_dma_dispatch(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
                              int M, int N, int K, int kind, const Epi& epi, int vec_ok,
-                             int group_m, hipStream_t st) {
+                             int group_m, hipStream_t st, int splits = 1) {
   const int tn = (N + BN - 1) / BN, tm = (M + BM - 1) / BM;
-  dim3 grid(tm * tn), block(64 * WGM * WGN);
+  dim3 grid(tm * tn, splits), block(64 * WGM * WGN);
 #define T2I_DMA_CASE(K_)                                                                      \
   case K_:                                                                                    \
     hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, ST, K_, AUX, XNone>), grid, block, 0, st, \
@@ -860,10 +975,82 @@ hipError_t gemm_dma_dispatch(const bf16* A, int lda, const bf16* W, int ldw, con
     T2I_DMA_CASE(EPI_RESID_GATED)
     T2I_DMA_CASE(EPI_SPLIT_VT)
     T2I_DMA_CASE(EPI_STORE_F32)
+    T2I_DMA_CASE(EPI_SILU)
+    case EPI_PARTIAL:   // (narrow tiles only: layers of few rows)
+      if constexpr (BM < 256) {
+        hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, ST, EPI_PARTIAL, AUX, XNone>), grid,
+                           block, 0, st, A, lda, W, ldw, bias, M, N, K, epi, tn, group_m, vec_ok,
+                           XNone{});
+        break;
+      }
+      return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 #undef T2I_DMA_CASE
   return hipGetLastError();
+}
+
+// Projections below 2048 rows on narrower tiles with deeper rings and many
+// waves.  One workgroup per CU (the rings take most of the LDS), so a launch
+// costs about (rounds of 256 tiles) x (the tile's bytes per K step,
+// proportional to BM + BN); the smallest estimate wins, ties to the larger
+// tile.  These tiles are bound by the latency of the fragment reads and
+// barriers of each K step, not by the loads (without any tile loads 1024 x
+// 1152 x 4608 still took 29 of 38 us on two waves of 16 x 144), so each tile
+// is cut into 6 to 16 waves: one wave's reads run under another's MFMAs.
+// Measured against 2, 4 and 8 waves of 16 x 144 per tile (1024 rows): 1152 x
+// 4608 38.2 -> 29.2 us, 1152 x 1152 12.3 -> 10.0, 4608 x 1152 with GELU
+// 19.4 -> 17.3, 3456 x 1152 18.9 -> 16.2; 4 waves of 32 x 144 per 128-row tile
+// were slower (23.5 us).  Every output element accumulates the same MFMAs in
+// the same K order as in every other GEMM path, so results do not depend on
+// the choice.
+// splits > 1: EPI_PARTIAL, K per slice (grid row).
+bool gemm_dma_small_fits(int M, int N) {
+  // widths of whole 144- or 128-column tiles; any multiple of 64 for up to two
+  // 32-row tiles
+  return N % 144 == 0 || N % 128 == 0 || (N % 64 == 0 && M <= 64);
+}
+
+hipError_t launch_gemm_dma_small(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
+                                 int M, int N, int K, int kind, const Epi& epi, int vec_ok,
+                                 hipStream_t st, int splits) {
+  long best = -1;
+  int bm = 0, bn = 0;
+  auto consider = [&](int m, int n) {
+    if (N % n) return;
+    const long tiles = (long)((M + m - 1) / m) * (N / n) * splits;
+    const long cost = (tiles + 255) / 256 * (m + n);
+    if (best < 0 || cost < best) {
+      best = cost;
+      bm = m;
+      bn = n;
+    }
+  };
+  if (N % 144 == 0) {
+    consider(128, 144);
+    consider(64, 144);
+    consider(32, 144);
+  } else {
+    consider(128, 192);
+    consider(128, 128);
+    consider(64, 128);
+    consider(32, 128);
+  }
+  consider(32, 64);
+#define T2I_SMALL(BM_, BN_, WGM_, WGN_, ST_, GM_)                                                \
+  if (bm == BM_ && bn == BN_)                                                                    \
+    return gemm_dma_dispatch<BM_, BN_, WGM_, WGN_, ST_, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, \
+                                                           vec_ok, GM_, st, splits);
+  T2I_SMALL(128, 144, 4, 3, 4, 8)
+  T2I_SMALL(64, 144, 4, 3, 5, 8)
+  T2I_SMALL(32, 144, 2, 3, 6, 16)
+  T2I_SMALL(128, 192, 4, 3, 3, 8)
+  T2I_SMALL(128, 128, 4, 4, 4, 8)
+  T2I_SMALL(64, 128, 4, 4, 5, 8)
+  T2I_SMALL(32, 128, 2, 4, 6, 16)
+  T2I_SMALL(32, 64, 2, 4, 7, 16)
+#undef T2I_SMALL
+  return hipErrorInvalidValue;
 }
 
 // Large-M projections (tile shapes and orders measured on MI355X at the DiT's
@@ -873,42 +1060,20 @@ hipError_t gemm_dma_dispatch(const bf16* A, int lda, const bf16* W, int ldw, con
 // averages ~17.  Bytes per FLOP -- (BM + BN) / (BM BN) -- and the L2 reuse of
 // the tile order decide, together with filling whole rounds of 256
 // workgroups:
-//   256 x 288 (8 waves of 64 x 144) where N is a multiple of 288 and its
-//             rounds cost less (fc1: N = 4608, M = 8192 -> 512 tiles);
-//   256 x 256 for long K where N is a multiple of 256 with whole rounds
-//             (joint-attention MLP up-projection: N = 12288 -> 768 tiles);
+//   256 x 288 (12 waves of 64 x 96) where N is a multiple of 288 and its
+//             rounds cost less (fc1: N = 4608, M = 8192 -> 512 tiles; with 8
+//             waves of 64 x 144 its GELU epilogue overlapped less: 88.1 ->
+//             84.4 us there, 123 -> 118 for 12 032 x 1152 x 4608);
+//   256 x 256 (16 waves of 64 x 64, same reason: 255.5 -> 250 us at 4096 x
+//             12288 x 3072) for long K where N is a multiple of 256 with whole
+//             rounds (joint-attention MLP up-projection: N = 12288 -> 768
+//             tiles);
 //   256 x 144 (8 waves of 32 x 144, three stages) for the other DiT widths;
 //   256 x 192 (8 waves of 64 x 96) where that fills whole rounds (N = 3072);
 //   256 x 128 otherwise.
 // Row blocks per tile group (see gemm_dma_kernel): 8 for long K, 2 for the
 // 288-wide tiles at short K, 1 for the 144-wide residual updates.  All load
 // with cache policy bit 0 (sc0) set, which measured faster.
-// Projections of a few hundred to ~2000 rows (the 512-px DiT's 1024, the
-// single small requests of a packed batch) on narrower tiles with deeper
-// rings: there the register-staged kernel waits a load latency per K step.
-// Row height 128, 64 or 32: one workgroup per CU (the rings take most of the
-// LDS), so a launch costs about (rounds of 256 tiles) x (the tile's bytes per
-// K step, proportional to BM + 144); the smallest estimate wins, ties to the
-// taller tile (1024 rows: 32 x 144 for the 1152-wide layers -> 256 tiles,
-// 128 x 144 for qkv and fc1).  Every output element accumulates the same
-// MFMAs in the same K order as in every other GEMM path, so results do not
-// depend on the choice.
-hipError_t launch_gemm_dma_small(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
-                                 int M, int N, int K, int kind, const Epi& epi, int vec_ok,
-                                 hipStream_t st) {
-  const long tn = N / 144;
-  auto cost = [&](int bm) { return ((((M + bm - 1) / bm) * tn + 255) / 256) * (bm + 144); };
-  const long c128 = cost(128), c64 = cost(64), c32 = cost(32);
-  if (c128 <= c64 && c128 <= c32)
-    return gemm_dma_dispatch<128, 144, 8, 1, 4, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok,
-                                                   8, st);
-  if (c64 <= c32)
-    return gemm_dma_dispatch<64, 144, 4, 1, 5, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok,
-                                                  8, st);
-  return gemm_dma_dispatch<32, 144, 2, 1, 6, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok,
-                                                16, st);
-}
-
 hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
                            int M, int N, int K, int kind, const Epi& epi, int vec_ok,
                            hipStream_t st) {
@@ -921,11 +1086,11 @@ hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const
   if (N % 288 == 0) {
     const long r288 = (mt * (N / 288) + 255) / 256, r144 = (mt * (N / 144) + 255) / 256;
     if (r288 * 9 <= r144 * 5)
-      return gemm_dma_dispatch<256, 288, 4, 2, 2, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi,
+      return gemm_dma_dispatch<256, 288, 4, 3, 2, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi,
                                                      vec_ok, longk ? 8 : 2, st);
   }
   if (longk && N % 256 == 0 && (mt * (N / 256)) % 256 == 0)
-    return gemm_dma_dispatch<256, 256, 4, 2, 2, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok,
+    return gemm_dma_dispatch<256, 256, 4, 4, 2, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok,
                                                    8, st);
   if (N % 144 == 0) {
     const int gm = longk ? 8 : (kind == EPI_RESID || kind == EPI_RESID_GATED) ? 1 : 8;
