@@ -30,11 +30,8 @@ namespace t2i {
 
 hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
                            int M, int N, int K, int kind, const Epi& epi, int vec_ok,
-                           hipStream_t st);
-hipError_t launch_gemm_dma_small(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
-                                 int M, int N, int K, int kind, const Epi& epi, int vec_ok,
-                                 hipStream_t st, int splits = 1);
-bool gemm_dma_small_fits(int M, int N);
+                           hipStream_t st, int splits = 1);
+bool gemm_dma_fits(int M, int N);
 
 // Map launch order -> tile order so XCD x (blocks b with b % 8 == x) owns the
 // contiguous tile range of its share.
@@ -449,23 +446,19 @@ hipError_t launch_gemm_bf16(const bf16* A, int lda, const bf16* W, int ldw, cons
   const int vec_ok = (epi.ldo % 4 == 0) && (epi.ldx % 4 == 0) && (epi.ld_gate % 4 == 0) &&
                      al(bias, 8) && al(epi.out, kind == EPI_STORE_F32 ? 16 : 8) &&
                      al(epi.x, 16) && al(epi.xb, 8) && al(epi.gate, 16);
-  // Tile choice.  Large M: 256-row tiles fed by direct HBM->LDS loads
-  // (gemm_dma.hip).  The DiT widths 1152, 2304, 3456 and 4608 are multiples of
-  // 144, so at M = 8192 the layers launch 256 / 512 / 768 / 1024 tiles --
-  // whole rounds on 256 CUs at one workgroup each; widths that are multiples
-  // of 128 take 192- or 128-wide tiles.  Otherwise 128 x 144 or 128 x 128
-  // register-staged tiles (the faster ones at M ~ 1000 measured), with K
-  // split over several workgroups when there are too few tiles to fill the
-  // chip (e.g. the 512-row text stream against K = 3072 or 12288).
-  // (the direct-load kernels address each operand with 32-bit byte offsets)
-  const bool dma_fits = (size_t)2 * M * lda < 0x7fffffff && (size_t)2 * N * ldw < 0x7fffffff;
-  if (M >= 2048 && (N % 144 == 0 || N % 128 == 0) && dma_fits)
+  // Direct HBM->LDS loads (gemm_dma.hip) for widths of whole tiles, with K
+  // split over several workgroups where the caller allows it and a layer of
+  // few rows against a long K would leave CUs idle (e.g. the 512-row text
+  // stream against K = 3072 or 12288); register-staged tiles for other widths
+  // and for operands past the direct loads' 32-bit byte offsets.
+  const bool dma = (size_t)2 * M * lda < 0x7fffffff && (size_t)2 * N * ldw < 0x7fffffff &&
+                   gemm_dma_fits(M, N);
+  // (from 2048 rows on there are tiles enough without splitting K)
+  int splits = splitk_ws && kind != EPI_SILU && !(dma && M >= 2048) ? splitk_factor(N, K) : 1;
+  if ((size_t)splits * M * N > splitk_floats) splits = 1;
+  if (splits == 1 && dma)
     return launch_gemm_dma(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
-  const int splits = splitk_ws ? splitk_factor(N, K) : 1;
-  const bool small_dma = dma_fits && K % 64 == 0 && gemm_dma_small_fits(M, N);
-  if (splits == 1 && small_dma)
-    return launch_gemm_dma_small(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
-  if (splits > 1 && (size_t)splits * M * N <= splitk_floats && kind != EPI_SILU) {
+  if (splits > 1) {
     Epi pe;
     std::memset(&pe, 0, sizeof(pe));
     pe.out = splitk_ws;
@@ -475,8 +468,8 @@ hipError_t launch_gemm_bf16(const bf16* A, int lda, const bf16* W, int ldw, cons
     // idle; same K order, same sums
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     hipError_t err =
-        small_dma ? launch_gemm_dma_small(A, lda, W, ldw, bias, M, N, K / splits, EPI_PARTIAL, pe,
-                                          pvec, st, splits)
+        dma ? launch_gemm_dma(A, lda, W, ldw, bias, M, N, K / splits, EPI_PARTIAL, pe, pvec, st,
+                              splits)
         : t128 * splits < 256
             ? gemm_bf16_dispatch<64, 64, 2>(A, lda, W, ldw, bias, M, N, K / splits, EPI_PARTIAL,
                                             pe, pvec, st, splits)

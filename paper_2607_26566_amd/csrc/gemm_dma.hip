@@ -175,18 +175,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   // this lane's byte offset of every block it loads, from A or W (the k
   // position is added per tile as the scalar offset); load round i takes block
   // wave + i NW: of A while that is below ABLK (a round may hold both)
-  // (256-row tiles are launched with whole column tiles only: their W rows are
-  // uniform steps from the first one, which go into the scalar offset)
   constexpr int ARND = ABLK / NW;
-  constexpr bool NWHOLE = BM == 256 && ABLK % NW == 0;
-  uint32_t src[NWHOLE ? ARND + 1 : BPW];
+  uint32_t src[BPW];
   int dst[BPW];   // byte offset of the block inside a stage (wave-uniform)
 #pragma unroll
   for (int i = 0; i < BPW; ++i) {
     int b = wave + i * NW;
     if (b >= TBLK) b -= NW;               // repeat this wave's previous block
     dst[i] = b * 1024;
-    if (NWHOLE && i > ARND) continue;
     const bool is_a = b < ABLK;
     const int lr = (is_a ? b : b - ABLK) * 8 + (lane >> 3);       // row within A or W tile
     const int c = (lane & 7) ^ ((lr >> 1) & 7);                   // logical chunk of this slot
@@ -202,13 +198,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
       wave + ARND * NW < ABLK ? (void*)A : (void*)W, 0, 0x7fffffff, 0x00020000);
   // load i of K step t into the slot at byte offset `slot`
   auto issue1 = [&](int i, int t, uint32_t slot) {
-    const int kb = t * 128;   // byte offset of the tile's 64 k values
-    if (NWHOLE && i > ARND)
-      dma16<AUX>(rw, (char*)smem + slot + dst[i], src[ARND],
-                 kb + (dst[i] - dst[ARND]) / 1024 * 16 * ldw);
-    else
-      dma16<AUX>(i < ARND ? ra : i == ARND && ABLK % NW ? rmix : rw, (char*)smem + slot + dst[i],
-                 src[NWHOLE ? min(i, ARND) : i], kb);
+    // (scalar offset: the tile's 64 k values)
+    dma16<AUX>(i < ARND ? ra : i == ARND && ABLK % NW ? rmix : rw, (char*)smem + slot + dst[i],
+               src[i], t * 128);
   };
   auto issue = [&](int t, int stage) {
 #pragma unroll
@@ -344,7 +336,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   // loop.
   constexpr int REGS = TM * TN * 4 + 2 * (TM + TN) * 4 + (PREX ? TM * TN * 4 : 0);
   constexpr bool HALF_STEP = ST >= 3 && BM < 256 && REGS <= 176;
-  constexpr bool ROLL = BM == 256 && BN != 144 && BN != 288 && NW == 8;
+  // The 256-row tiles of 8 waves x (64 rows x 64 or 96 columns) keep the MFMAs
+  // going across the barrier: the two A fragment sets of a K step alternate,
+  // and each W fragment is read again, for the next half-step, as soon as its
+  // column's MFMAs have been issued; the workgroup meets a third of the way
+  // into half-step 1, when its fragments are long in registers, and the tile
+  // loads into the freed stage follow one or two per column.  Same MFMAs in the
+  // same order.  256 x 192: 4096 x 3072 x 3072 72.9 -> 70.8 us, 3600 x 3072 x
+  // 12288 267 -> 252 (from memory), 256 x 128: 2048 x 3072 x 3072 46.2 -> 41;
+  // 4096 x 3072 x 12288 277 either way when its operands come from memory.
+  // Slower or equal for 256 x 144 (one wave's 32 x 144: 27.1 -> 27.9 us) and 256
+  // x 288 (its registers spill).
+  constexpr bool ROLL = BM == 256 && (BN == 192 || BN == 128) && NW == 8;
   if constexpr (ROLL) {
     // this lane's byte offset in a 16-row fragment (the swizzle depends on the
     // row within it alone); half-step 1 flips bit 6
@@ -990,125 +993,97 @@ hipError_t gemm_dma_dispatch(const bf16* A, int lda, const bf16* W, int ldw, con
   return hipGetLastError();
 }
 
-// Projections below 2048 rows on narrower tiles with deeper rings and many
-// waves.  One workgroup per CU (the rings take most of the LDS), so a launch
-// costs about (rounds of 256 tiles) x (the tile's bytes per K step,
-// proportional to BM + BN); the smallest estimate wins, ties to the larger
-// tile.  These tiles are bound by the latency of the fragment reads and
+// Tile shapes, in the order tried (ties to the earlier, larger one): rows,
+// columns, and the cost of one round of 256 workgroups in hundredths of a
+// microsecond per K step of 64, from K = 2048 on (measured on MI355X at K =
+// 3072 .. 12288, rounds from half full on) and below (K = 1152, scaled alike:
+// there the prologue and epilogue weigh differently).
+//
+// One workgroup per CU (the rings take most of the LDS), so a launch costs its
+// rounds times the tile's cost; the cheapest shape that divides N is taken.
+// The tall tiles move the fewest bytes per FLOP, the low ones fill the chip
+// where a tall one would leave a round partly empty: 2640 x 3456 x 1152 takes
+// 34 us in two rounds of 256 x 144 (264 tiles) and 27 in one of 256 x 192;
+// 2400 x 9216 x 3072 146 and 127; 3600 x 3072 x 12288 307 (256 x 128, two
+// rounds) and 236 (256 x 192, one).
+//
+// Up to 128 rows a tile is bound by the latency of the fragment reads and
 // barriers of each K step, not by the loads (without any tile loads 1024 x
-// 1152 x 4608 still took 29 of 38 us on two waves of 16 x 144), so each tile
-// is cut into 6 to 16 waves: one wave's reads run under another's MFMAs.
-// Measured against 2, 4 and 8 waves of 16 x 144 per tile (1024 rows): 1152 x
-// 4608 38.2 -> 29.2 us, 1152 x 1152 12.3 -> 10.0, 4608 x 1152 with GELU
-// 19.4 -> 17.3, 3456 x 1152 18.9 -> 16.2; 4 waves of 32 x 144 per 128-row tile
-// were slower (23.5 us).  Every output element accumulates the same MFMAs in
-// the same K order as in every other GEMM path, so results do not depend on
-// the choice.
-// splits > 1: EPI_PARTIAL, K per slice (grid row).
-bool gemm_dma_small_fits(int M, int N) {
-  // widths of whole 144- or 128-column tiles; any multiple of 64 for up to two
-  // 32-row tiles
+// 1152 x 4608 still took 29 of 38 us on two waves of 16 x 144), so it is cut
+// into 6 to 16 waves: one wave's reads run under another's MFMAs.  Measured
+// against 2, 4 and 8 waves of 16 x 144 per tile (1024 rows): 1152 x 4608
+// 38.0 -> 27.0 us, 1152 x 1152 12.7 -> 9.6, 4608 x 1152 with GELU 19.1 -> 16.8;
+// 4 waves of 32 x 144 per 128-row tile were slower (23.5 us).  The widest
+// tiles run on 12 (256 x 288) and 16 waves (256 x 256), so that the GELU
+// arithmetic of one wave's epilogue overlaps more of the others' loops: 87.9
+// -> 83.9 us at 8192 x 4608 x 1152, 262 -> 248 at 4096 x 12288 x 3072, against
+// 8 waves each; 256 x 144 and 256 x 192 were not faster with 12.
+//
+// Every output element accumulates the same MFMAs in the same K order in all
+// of them (and in the other GEMM paths), so results do not depend on the
+// choice.  All load with cache policy bit 0 (sc0) set, which measured faster.
+struct DmaTile {
+  int bm, bn, cost, cost_short;
+};
+constexpr DmaTile kDmaTiles[] = {
+    {256, 288, 176, 195}, {256, 256, 165, 205}, {256, 192, 128, 133}, {256, 144, 113, 105},
+    {256, 128, 95, 108},  {128, 192, 78, 78},   {128, 144, 68, 68},   {128, 128, 53, 53},
+    {64, 144, 45, 45},    {64, 128, 42, 42},    {32, 144, 37, 37},    {32, 128, 35, 35},
+    {32, 64, 25, 25},
+};
+
+// widths of whole 144- or 128-column tiles; any multiple of 64 for up to two
+// 32-row tiles
+bool gemm_dma_fits(int M, int N) {
   return N % 144 == 0 || N % 128 == 0 || (N % 64 == 0 && M <= 64);
 }
 
-hipError_t launch_gemm_dma_small(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
-                                 int M, int N, int K, int kind, const Epi& epi, int vec_ok,
-                                 hipStream_t st, int splits) {
-  long best = -1;
-  int bm = 0, bn = 0;
-  auto consider = [&](int m, int n) {
-    if (N % n) return;
-    const long tiles = (long)((M + m - 1) / m) * (N / n) * splits;
-    const long cost = (tiles + 255) / 256 * (m + n);
-    if (best < 0 || cost < best) {
-      best = cost;
-      bm = m;
-      bn = n;
-    }
-  };
-  if (N % 144 == 0) {
-    consider(128, 144);
-    consider(64, 144);
-    consider(32, 144);
-  } else {
-    consider(128, 192);
-    consider(128, 128);
-    consider(64, 128);
-    consider(32, 128);
-  }
-  consider(32, 64);
-#define T2I_SMALL(BM_, BN_, WGM_, WGN_, ST_, GM_)                                                \
-  if (bm == BM_ && bn == BN_)                                                                    \
-    return gemm_dma_dispatch<BM_, BN_, WGM_, WGN_, ST_, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, \
-                                                           vec_ok, GM_, st, splits);
-  T2I_SMALL(128, 144, 4, 3, 4, 8)
-  T2I_SMALL(64, 144, 4, 3, 5, 8)
-  T2I_SMALL(32, 144, 2, 3, 6, 16)
-  T2I_SMALL(128, 192, 4, 3, 3, 8)
-  T2I_SMALL(128, 128, 4, 4, 4, 8)
-  T2I_SMALL(64, 128, 4, 4, 5, 8)
-  T2I_SMALL(32, 128, 2, 4, 6, 16)
-  T2I_SMALL(32, 64, 2, 4, 7, 16)
-#undef T2I_SMALL
-  return hipErrorInvalidValue;
-}
-
-// Large-M projections (tile shapes and orders measured on MI355X at the DiT's
-// and the joint-attention model's shapes).  Operand loads that miss the XCD's
-// L2 bound these GEMMs: a CU takes 30-57 bytes per clock of direct loads from
-// L2 but only 10-13 from the memory-side cache or HBM, and in these GEMMs it
-// averages ~17.  Bytes per FLOP -- (BM + BN) / (BM BN) -- and the L2 reuse of
-// the tile order decide, together with filling whole rounds of 256
-// workgroups:
-//   256 x 288 (12 waves of 64 x 96) where N is a multiple of 288 and its
-//             rounds cost less (fc1: N = 4608, M = 8192 -> 512 tiles; with 8
-//             waves of 64 x 144 its GELU epilogue overlapped less: 88.1 ->
-//             84.4 us there, 123 -> 118 for 12 032 x 1152 x 4608);
-//   256 x 256 (16 waves of 64 x 64, same reason: 255.5 -> 250 us at 4096 x
-//             12288 x 3072) for long K where N is a multiple of 256 with whole
-//             rounds (joint-attention MLP up-projection: N = 12288 -> 768
-//             tiles);
-//   256 x 144 (8 waves of 32 x 144, three stages) for the other DiT widths;
-//   256 x 192 (8 waves of 64 x 96) where that fills whole rounds (N = 3072);
-//   256 x 128 otherwise.
-// Row blocks per tile group (see gemm_dma_kernel): 8 for long K, 2 for the
-// 288-wide tiles at short K, 1 for the 144-wide residual updates.  All load
-// with cache policy bit 0 (sc0) set, which measured faster.
+// splits > 1: EPI_PARTIAL, K per slice (grid row).
 hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
                            int M, int N, int K, int kind, const Epi& epi, int vec_ok,
-                           hipStream_t st) {
-  const long mt = (M + 255) / 256;
+                           hipStream_t st, int splits) {
   const bool longk = K >= 2048;
-  // 288 wide where its rounds cost less: a round of 256 x 288 tiles takes
-  // ~1.8x a round of 256 x 144 tiles (measured at 8192 rows), so the wider
-  // tile wins when it needs fewer than 5/9 of the rounds (fc1 at 8192 rows:
-  // 2 rounds against 4; the 1152-wide layers at 12 032 rows: 1 against 2)
-  if (N % 288 == 0) {
-    const long r288 = (mt * (N / 288) + 255) / 256, r144 = (mt * (N / 144) + 255) / 256;
-    if (r288 * 9 <= r144 * 5)
-      return gemm_dma_dispatch<256, 288, 4, 3, 2, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi,
-                                                     vec_ok, longk ? 8 : 2, st);
-  }
-  if (longk && N % 256 == 0 && (mt * (N / 256)) % 256 == 0)
-    return gemm_dma_dispatch<256, 256, 4, 4, 2, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok,
-                                                   8, st);
-  if (N % 144 == 0) {
-    const int gm = longk ? 8 : (kind == EPI_RESID || kind == EPI_RESID_GATED) ? 1 : 8;
-    const long tiles = mt * (N / 144);
-    if (kind == EPI_SPLIT_VT && vec_ok && M % 256 == 0 && K == 18 * 64 && epi.vcol0 % 144 == 0 &&
-        tiles > 256 && tiles <= (long)kPipeTiles * 256) {
-      hipLaunchKernelGGL(gemm_dma_vt_pipe_kernel, dim3(256), dim3(512), 0, st, A, lda, W, ldw, bias,
-                         M, N, epi, N / 144, gm, (int)tiles);
-      return hipGetLastError();
+  DmaTile t{0, 0, 0, 0};
+  long best = -1, tiles = 0;
+  for (const DmaTile& c : kDmaTiles) {
+    if (N % c.bn || (kind == EPI_PARTIAL && c.bm == 256)) continue;
+    const long n = (long)((M + c.bm - 1) / c.bm) * (N / c.bn) * splits;
+    const long cost = (n + 255) / 256 * (longk ? c.cost : c.cost_short);
+    if (best < 0 || cost < best) {
+      best = cost;
+      t = c;
+      tiles = n;
     }
-    return gemm_dma_dispatch<256, 144, 8, 1, 3, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok,
-                                                   gm, st);
   }
-  if (N % 192 == 0 && (mt * (N / 192)) % 256 == 0)
-    return gemm_dma_dispatch<256, 192, 4, 2, 2, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok,
-                                                   8, st);
-  return gemm_dma_dispatch<256, 128, 4, 2, 3, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, 8,
-                                                 st);
+  // row blocks per tile group (see gemm_dma_kernel): 8 for long K, 2 for the
+  // 288-wide tiles at short K, 1 for the 144-wide residual updates
+  const bool resid = kind == EPI_RESID || kind == EPI_RESID_GATED;
+  const int gm144 = longk || !resid ? 8 : 1;
+  if (t.bm == 256 && t.bn == 144 && kind == EPI_SPLIT_VT && vec_ok && M % 256 == 0 &&
+      K == 18 * 64 && epi.vcol0 % 144 == 0 && tiles > 256 && tiles <= (long)kPipeTiles * 256) {
+    hipLaunchKernelGGL(gemm_dma_vt_pipe_kernel, dim3(256), dim3(512), 0, st, A, lda, W, ldw, bias,
+                       M, N, epi, N / 144, gm144, (int)tiles);
+    return hipGetLastError();
+  }
+#define T2I_TILE(BM_, BN_, WGM_, WGN_, ST_, GM_)                                                  \
+  if (t.bm == BM_ && t.bn == BN_)                                                                 \
+    return gemm_dma_dispatch<BM_, BN_, WGM_, WGN_, ST_, 1>(A, lda, W, ldw, bias, M, N, K, kind, epi, \
+                                                           vec_ok, GM_, st, splits);
+  T2I_TILE(256, 288, 4, 3, 2, longk ? 8 : 2)
+  T2I_TILE(256, 256, 4, 4, 2, 8)
+  T2I_TILE(256, 192, 4, 2, 2, 8)
+  T2I_TILE(256, 144, 8, 1, 3, gm144)
+  T2I_TILE(256, 128, 4, 2, 3, 8)
+  T2I_TILE(128, 192, 4, 3, 3, 8)
+  T2I_TILE(128, 144, 4, 3, 4, 8)
+  T2I_TILE(128, 128, 4, 4, 4, 8)
+  T2I_TILE(64, 144, 4, 3, 5, 8)
+  T2I_TILE(64, 128, 4, 4, 5, 8)
+  T2I_TILE(32, 144, 2, 3, 6, 16)
+  T2I_TILE(32, 128, 2, 4, 6, 16)
+  T2I_TILE(32, 64, 2, 4, 7, 16)
+#undef T2I_TILE
+  return hipErrorInvalidValue;
 }
 
 // The cross-attention query projection with the cross-attention fused in
