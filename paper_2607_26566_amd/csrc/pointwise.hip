@@ -602,9 +602,10 @@ constexpr int kLoraRows = 64, kLoraMaxRank = 128;
 
 template <typename T, int RK>
 __global__ __launch_bounds__(256) void lora_merge_kernel(int n_out, int n_in, int rank, float alpha,
-                                                         T* __restrict__ W, int ldw,
-                                                         const T* __restrict__ A,
-                                                         const T* __restrict__ B) {
+                                                         LoraGroup g, int ldw) {
+  T* __restrict__ W = (T*)g.W[blockIdx.z];
+  const T* __restrict__ A = (const T*)g.A[blockIdx.z];
+  const T* __restrict__ B = (const T*)g.B[blockIdx.z];
   __shared__ float brow[kLoraRows][RK];
   const int i = blockIdx.x * 256 + threadIdx.x;
   const int o0 = blockIdx.y * kLoraRows;
@@ -635,105 +636,141 @@ __global__ __launch_bounds__(256) void lora_merge_kernel(int n_out, int n_in, in
   }
 }
 
-// bf16 LoRA merge on MFMA.  A workgroup (4 waves) owns a 64-row x 128-column
-// tile of W.  It first issues the loads of its W tile (16 bytes per lane,
-// rows contiguous, four per thread, so the HBM reads are in flight from the
-// start), then stages the tile's rank slice of B [64][RK] and of A,
-// transposed to [128][RK] (k contiguous, as both MFMA operands want it), in
-// LDS, zero-padded past `rank`; each wave computes two 32x32 tiles of B A on
-// v_mfma_f32_32x32x16_bf16 (fp32 accumulation over the rank), writes them to
-// LDS as fp32, and every thread then finishes its W chunks: W + alpha (B A),
-// rounded once to bf16.  Needs n_in % 8 == 0, ldw % 8 == 0 and 16-byte
-// aligned W and A rows (the launcher checks and falls back otherwise).
-constexpr int kLoraTM = 64, kLoraTN = 128;
+// bf16 LoRA merge on MFMA, bound by reading and writing W.  A workgroup of 4
+// waves owns 64 columns of W and `steps` x 128 rows: it transposes its 64
+// columns of A through LDS once, every wave keeps them as MFMA fragments in
+// registers (k contiguous, zero past `rank`), and then walks its rows 32 at a
+// time -- the rows of B straight from memory as the other operand, the product
+// on v_mfma_f32_32x32x16_bf16 (fp32 accumulation over the rank), turned from
+// the MFMA layout to row chunks in the wave's own part of LDS, added to W and
+// rounded once.  The next rows' W and B are fetched before the current ones
+// are finished.  Needs n_in % 8 == 0, ldw % 8 == 0 and 16-byte aligned W and A
+// (the launcher checks).  28 weights of 3456 x 1152: 138 -> 90 us at rank 64
+// (5.1 TB/s), 86 -> 73 at rank 16 (6.2 TB/s), 271 -> 149 at rank 128, against
+// one 64 x 128 tile per workgroup with both operands transposed through LDS.
+constexpr int kLoraTN = 64;
 
 template <int RK>
 __global__ __launch_bounds__(256) void lora_merge_mfma_kernel(int n_out, int n_in, int rank,
-                                                              float alpha, LoraGroup g, int ldw) {
+                                                              float alpha, LoraGroup g, int ldw,
+                                                              int steps) {
   // weight blockIdx.z of the group
   bf16* __restrict__ W = (bf16*)g.W[blockIdx.z];
   const bf16* __restrict__ A = (const bf16*)g.A[blockIdx.z];
   const bf16* __restrict__ B = (const bf16*)g.B[blockIdx.z];
-  constexpr int KP = RK + 8;                         // LDS row pitch of the operands (bf16)
-  constexpr int PP = kLoraTN + 4;                    // LDS row pitch of the product (fp32)
-  constexpr int OPS = (kLoraTM + kLoraTN) * KP * 2;  // operand bytes
-  constexpr int PRB = kLoraTM * PP * 4;              // product bytes
-  __shared__ __attribute__((aligned(16))) char smem[OPS > PRB ? OPS : PRB];
-  bf16* Bs = (bf16*)smem;                  // [64][KP]
-  bf16* At = Bs + kLoraTM * KP;            // [128][KP]
-  float* Ps = (float*)smem;                // [64][PP], after the MFMAs
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int o0 = blockIdx.y * kLoraTM, i0 = blockIdx.x * kLoraTN;
-
-  // this thread's W chunks: row (tid >> 4) + 16 c, 8 columns at 8 (tid & 15)
-  constexpr int NC = kLoraTM * kLoraTN / 8 / 256;
-  const int cc = (tid & 15) * 8;
-  bf16x8 wv[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int o = o0 + (tid >> 4) + 16 * c, i = i0 + cc;
-    wv[c] = bf16x8{};
-    if (o < n_out && i < n_in) wv[c] = *(const bf16x8*)(W + (size_t)o * ldw + i);
-  }
-  // operands into LDS, zero past rank / the matrix edges
-  for (int e = tid; e < kLoraTM * (RK / 8); e += 256) {
-    const int r = e / (RK / 8), k = (e - r * (RK / 8)) * 8;
-    bf16x8 v = bf16x8{};
-    if (o0 + r < n_out)
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (k + j < rank) v[j] = B[(size_t)(o0 + r) * rank + k + j];
-    *(bf16x8*)(Bs + r * KP + k) = v;
-  }
-  for (int e = tid; e < RK * (kLoraTN / 8); e += 256) {
-    const int k = e / (kLoraTN / 8), c = (e - k * (kLoraTN / 8)) * 8;
-    bf16x8 v = bf16x8{};
-    if (k < rank && i0 + c < n_in) v = *(const bf16x8*)(A + (size_t)k * n_in + i0 + c);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) At[(c + j) * KP + k] = v[j];
-  }
-  __syncthreads();
-  // wave w: rows 32 (w & 1) .., columns 64 (w >> 1) .. (two 32-wide tiles)
+  constexpr int KP = RK + 8;        // LDS row pitch of A^T (bf16)
+  constexpr int PP = kLoraTN + 4;   // LDS row pitch of the product (fp32)
+  constexpr int ABYTES = kLoraTN * KP * 2, PBYTES = 4 * 32 * PP * 4;
+  __shared__ __attribute__((aligned(16))) char smem[ABYTES > PBYTES ? ABYTES : PBYTES];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i0 = blockIdx.x * kLoraTN;
   const int l32 = lane & 31, hl = lane >> 5;
-  const int ro = 32 * (wave & 1), co = 64 * (wave >> 1);
-  f32x16 acc[2] = {f32x16{}, f32x16{}};
+  const int o_begin = (blockIdx.y * 4 + wave) * 32 * steps, o_end = min(o_begin + 32 * steps, n_out);
+  typedef bf16 bf16x8u __attribute__((ext_vector_type(8), aligned(2)));   // B's rows start anywhere
+
+  // W of rows o .. o + 31: four 16-byte chunks per lane, row 8 c + lane / 8,
+  // columns 8 (lane % 8) ..
+  const int wr = lane >> 3, wc = i0 + (lane & 7) * 8;
+  auto load_w = [&](int o, bf16x8 (&v)[4]) {
 #pragma unroll
-  for (int k = 0; k < RK; k += 16) {
-    const bf16x8 bo = *(const bf16x8*)(Bs + (ro + l32) * KP + k + 8 * hl);
+    for (int c = 0; c < 4; ++c) {
+      const int r = o + 8 * c + wr;
+      v[c] = bf16x8{};
+      if (r < o_end && wc < n_in) v[c] = *(const bf16x8*)(W + (size_t)r * ldw + wc);
+    }
+  };
+  auto load_b = [&](int o, bf16x8 (&v)[RK / 16]) {
+    const bf16* p = B + (size_t)min(o + l32, n_out - 1) * rank + 8 * hl;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const bf16x8 ai = *(const bf16x8*)(At + (co + 32 * t + l32) * KP + k + 8 * hl);
-      acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bo, ai, acc[t], 0, 0, 0);
+    for (int k = 0; k < RK / 16; ++k) {
+      v[k] = bf16x8{};
+      const int kk = 16 * k + 8 * hl;
+      if (kk + 8 <= rank) {
+        v[k] = *(const bf16x8u*)(p + 16 * k);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (kk + j < rank) v[k][j] = p[16 * k + j];
+      }
+    }
+  };
+  bf16x8 wv[4], bv[RK / 16];
+  if (o_begin < o_end) {
+    load_w(o_begin, wv);
+    load_b(o_begin, bv);
+  }
+  // A^T [64][KP], zero past rank / the matrix edge: a thread takes 8 rows k of
+  // one column chunk at a time, so that LDS is written 16 bytes of one column
+  bf16* At = (bf16*)smem;
+  for (int e = tid; e < (RK / 8) * (kLoraTN / 8); e += 256) {
+    const int k = e / (kLoraTN / 8) * 8, c = (e % (kLoraTN / 8)) * 8;
+    bf16x8 r[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      r[j] = bf16x8{};
+      if (k + j < rank && i0 + c < n_in) r[j] = *(const bf16x8*)(A + (size_t)(k + j) * n_in + i0 + c);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      bf16x8 t;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = r[j][q];
+      *(bf16x8*)(At + (c + q) * KP + k) = t;
     }
   }
-  __syncthreads();   // the operands are no longer read: the product takes their place
+  __syncthreads();
+  bf16x8 af[2][RK / 16];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-      Ps[(ro + 8 * (e >> 2) + 4 * hl + (e & 3)) * PP + co + 32 * t + l32] = acc[t][e];
-  __syncthreads();
+    for (int k = 0; k < RK / 16; ++k)
+      af[t][k] = *(const bf16x8*)(At + (32 * t + l32) * KP + 16 * k + 8 * hl);
+  __syncthreads();   // the product takes A^T's place
+
+  float* Ps = (float*)smem + wave * 32 * PP;
+  for (int o = o_begin; o < o_end; o += 32) {
+    f32x16 acc[2] = {f32x16{}, f32x16{}};
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int r = (tid >> 4) + 16 * c, o = o0 + r, i = i0 + cc;
-    if (o >= n_out || i >= n_in) continue;
-    const float4 p0 = *(const float4*)(Ps + r * PP + cc);
-    const float4 p1 = *(const float4*)(Ps + r * PP + cc + 4);
-    const float pv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
-    bf16x8 out;
+    for (int k = 0; k < RK / 16; ++k)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) out[j] = (bf16)fmaf(alpha, pv[j], (float)wv[c][j]);
-    *(bf16x8*)(W + (size_t)o * ldw + i) = out;
+      for (int t = 0; t < 2; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[t][k], bv[k], acc[t], 0, 0, 0);
+    // lane: row l32, columns 32 t + 8 q + 4 hl .. + 3
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *(f32x4*)&Ps[l32 * PP + 32 * t + 8 * q + 4 * hl] =
+            f32x4{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+    bf16x8 wn[4];
+    if (o + 32 < o_end) {
+      load_b(o + 32, bv);
+      load_w(o + 32, wn);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float* pr = &Ps[(8 * c + wr) * PP + (lane & 7) * 8];
+      const f32x4 p0 = *(const f32x4*)pr, p1 = *(const f32x4*)(pr + 4);
+      bf16x8 y;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) y[j] = (bf16)fmaf(alpha, j < 4 ? p0[j] : p1[j - 4], (float)wv[c][j]);
+      const int r = o + 8 * c + wr;
+      if (r < o_end && wc < n_in) *(bf16x8*)(W + (size_t)r * ldw + wc) = y;
+    }
+    if (o + 32 < o_end)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) wv[c] = wn[c];
   }
 }
 
 template <typename T>
-static hipError_t lora_dispatch(int n_out, int n_in, int rank, float alpha, void* W, int ldw,
-                                const void* A, const void* B, hipStream_t st) {
-  dim3 grid((n_in + 255) / 256, (n_out + kLoraRows - 1) / kLoraRows);
-#define T2I_LORA(RK_)                                                                        \
-  hipLaunchKernelGGL((lora_merge_kernel<T, RK_>), grid, dim3(256), 0, st, n_out, n_in, rank, \
-                     alpha, (T*)W, ldw, (const T*)A, (const T*)B)
+static hipError_t lora_dispatch(int n, int n_out, int n_in, int rank, float alpha,
+                                const LoraGroup& g, int ldw, hipStream_t st) {
+  dim3 grid((n_in + 255) / 256, (n_out + kLoraRows - 1) / kLoraRows, n);
+#define T2I_LORA(RK_)                                                                             \
+  hipLaunchKernelGGL((lora_merge_kernel<T, RK_>), grid, dim3(256), 0, st, n_out, n_in, rank, alpha, \
+                     g, ldw)
   if (rank <= 16) T2I_LORA(16);
   else if (rank <= 32) T2I_LORA(32);
   else if (rank <= 64) T2I_LORA(64);
@@ -761,10 +798,14 @@ hipError_t launch_lora_merge_group(bool bf16_io, int n, int n_out, int n_in, int
   for (int i = 0; i < n; ++i)
     vec = vec && (uintptr_t)g.W[i] % 16 == 0 && (uintptr_t)g.A[i] % 16 == 0;
   if (vec) {
-    dim3 grid((n_in + kLoraTN - 1) / kLoraTN, (n_out + kLoraTM - 1) / kLoraTM, n);
+    // 32-row steps per wave: several (they share the transposed A) while that
+    // leaves 2048 workgroups
+    const long tiles = (long)((n_in + kLoraTN - 1) / kLoraTN) * ((n_out + 127) / 128) * n;
+    const int steps = tiles >= 8192 ? 4 : tiles >= 4096 ? 2 : 1;
+    dim3 grid((n_in + kLoraTN - 1) / kLoraTN, (n_out + 128 * steps - 1) / (128 * steps), n);
 #define T2I_LORA_MF(RK_)                                                                       \
   hipLaunchKernelGGL((lora_merge_mfma_kernel<RK_>), grid, dim3(256), 0, st, n_out, n_in, rank, \
-                     alpha, g, ldw)
+                     alpha, g, ldw, steps)
     if (rank <= 16) T2I_LORA_MF(16);
     else if (rank <= 32) T2I_LORA_MF(32);
     else if (rank <= 64) T2I_LORA_MF(64);
@@ -772,14 +813,8 @@ hipError_t launch_lora_merge_group(bool bf16_io, int n, int n_out, int n_in, int
 #undef T2I_LORA_MF
     return hipGetLastError();
   }
-  for (int i = 0; i < n; ++i) {
-    hipError_t e = bf16_io ? lora_dispatch<bf16>(n_out, n_in, rank, alpha, g.W[i], ldw, g.A[i],
-                                                 g.B[i], st)
-                           : lora_dispatch<float>(n_out, n_in, rank, alpha, g.W[i], ldw, g.A[i],
-                                                  g.B[i], st);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return bf16_io ? lora_dispatch<bf16>(n, n_out, n_in, rank, alpha, g, ldw, st)
+                 : lora_dispatch<float>(n, n_out, n_in, rank, alpha, g, ldw, st);
 }
 
 __global__ void add_inplace_kernel(float* __restrict__ x, const float* __restrict__ r, size_t n) {
