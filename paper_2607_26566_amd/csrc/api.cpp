@@ -219,7 +219,9 @@ struct t2i_dit {
   size_t ws_bytes = 0;
   Layout L{};
   std::string err;
-  std::vector<CacheHeader> hdr_host;
+  // page-locked copy of the cache headers that the decision kernel writes
+  // itself (created by the first cache check)
+  CacheHeader* hdr_host = nullptr;
   // kernel timing
   uint32_t prof_mask = 0;
   std::vector<hipEvent_t> ev_pool;               // created on demand, reused
@@ -242,6 +244,7 @@ struct t2i_dit {
         (void)hipEventDestroy(blk_ev[b]);
       }
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
+    if (hdr_host) (void)hipHostFree(hdr_host);
   }
 
   template <typename T>
@@ -869,15 +872,15 @@ t2i_status cache_check_impl(t2i_dit* h, const Plan& P, int step, int n_steps, do
   double* partial = h->at<double>(h->L.partial);
   // block 0's first LN-modulation (MMDiT: of the image stream)
   const int sh = is_mmdit(h) ? 6 * c.hidden : 0;
+  if (!h->hdr_host)
+    HIP_TRY(h, hipHostMalloc((void**)&h->hdr_host, sizeof(CacheHeader) * kMaxReq,
+                             hipHostMallocDefault));
   HIP_TRY(h, prof_mark(h, T2I_K_CACHE, true, st));
   HIP_TRY(h, launch_cache_signal(h->at<float>(h->L.x0), P.rm, h->at<float>(h->L.mod),
                                  mod_width(c), sh, sh + c.hidden, c.hidden, c.ln_eps, cp.m_prev,
                                  cp.hdr, step, partial, st));
-  HIP_TRY(h, launch_cache_decide(P.rm, partial, cp.hdr, step, n_steps, tau, mode, st));
+  HIP_TRY(h, launch_cache_decide(P.rm, partial, cp.hdr, h->hdr_host, step, n_steps, tau, mode, st));
   HIP_TRY(h, prof_mark(h, T2I_K_CACHE, false, st));
-  h->hdr_host.resize(P.n_req);
-  HIP_TRY(h, hipMemcpyAsync(h->hdr_host.data(), cp.hdr, sizeof(CacheHeader) * P.n_req,
-                            hipMemcpyDeviceToHost, st));
   HIP_TRY(h, hipStreamSynchronize(st));
   for (int r = 0; r < P.n_req; ++r) {
     if (rel_l1) rel_l1[r] = h->hdr_host[r].d;

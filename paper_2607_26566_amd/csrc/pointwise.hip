@@ -799,9 +799,9 @@ hipError_t launch_lora_merge_group(bool bf16_io, int n, int n_out, int n_in, int
     vec = vec && (uintptr_t)g.W[i] % 16 == 0 && (uintptr_t)g.A[i] % 16 == 0;
   if (vec) {
     // 32-row steps per wave: several (they share the transposed A) while that
-    // leaves 2048 workgroups
+    // leaves 1024 workgroups or more
     const long tiles = (long)((n_in + kLoraTN - 1) / kLoraTN) * ((n_out + 127) / 128) * n;
-    const int steps = tiles >= 8192 ? 4 : tiles >= 4096 ? 2 : 1;
+    const int steps = tiles >= 8192 ? 4 : tiles >= 2048 ? 2 : 1;
     dim3 grid((n_in + kLoraTN - 1) / kLoraTN, (n_out + 128 * steps - 1) / (128 * steps), n);
 #define T2I_LORA_MF(RK_)                                                                       \
   hipLaunchKernelGGL((lora_merge_mfma_kernel<RK_>), grid, dim3(256), 0, st, n_out, n_in, rank, \
@@ -1178,11 +1178,14 @@ hipError_t launch_final_layer(const float* x, const ReqMap& rm, const void* w_ou
 // ---------------------------------------------------------------------------
 // Step-skip cache.
 //
-// cache_signal_kernel: workgroup = 16 rows of one request.  m = LNmod(x0;
-// block-0 shift_msa, scale_msa) in fp32; partial[blk] = (sum|m - m_prev|,
-// sum|m_prev|) in fp64 (lane order, butterfly, then waves 0..3); m_prev := m.
-// cache_decide_kernel: one thread per request sums its partials in block
-// order and applies the rule.
+// cache_signal_kernel: workgroup = 16 rows of one request, one wave each (a
+// wave that took four rows in turn paid their memory latency four times: 24.0
+// -> 7.4 us at 1408 rows).  m = LNmod(x0; block-0 shift_msa,
+// scale_msa) in fp32; partial[blk] = (sum|m - m_prev|, sum|m_prev|) in fp64
+// (lane order, butterfly, then waves 0..15); m_prev := m.
+// cache_decide_kernel: one wave per request sums its partials (lane l the
+// blocks l, l + 64, .. in order, then a butterfly), applies the rule and also
+// writes the header to page-locked host memory for the caller.
 
 int cache_partial_blocks(const ReqMap& rm) {
   int n = 0;
@@ -1191,12 +1194,15 @@ int cache_partial_blocks(const ReqMap& rm) {
   return n;
 }
 
-__global__ __launch_bounds__(256) void cache_signal_kernel(
+// NI: float4 per lane (D <= 256 NI)
+template <int NI>
+__global__ __launch_bounds__(64 * kCacheRowsPerBlock) void cache_signal_kernel(
     const float* __restrict__ x0, ReqMap rm, const float* __restrict__ mod, int ld_mod,
     int shift_off, int scale_off, int D, float eps, float* __restrict__ m_prev,
     const CacheHeader* __restrict__ hdr, int step, double* __restrict__ partial) {
-  __shared__ double red[4][2];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ double red[kCacheRowsPerBlock][2];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // block -> (request, row chunk)
   int r = 0, base = 0;
   for (;;) {
@@ -1205,32 +1211,31 @@ __global__ __launch_bounds__(256) void cache_signal_kernel(
     base += nb;
     ++r;
   }
-  const int chunk = blockIdx.x - base;
-  const bool have_prev = step > 0 && hdr[r].has_m;
-  const float* md = mod + (size_t)rm.modrow[r] * ld_mod;
-  const float4* sh = (const float4*)(md + shift_off);
-  const float4* sc = (const float4*)(md + scale_off);
   const int nv = D >> 2;
+  const int tok = rm.tok_off[r] + ((int)blockIdx.x - base) * kCacheRowsPerBlock + wave;
   double num = 0.0, den = 0.0;
-  for (int rr = 0; rr < kCacheRowsPerBlock / 4; ++rr) {
-    const int tok = rm.tok_off[r] + chunk * kCacheRowsPerBlock + wave * (kCacheRowsPerBlock / 4) + rr;
-    if (tok >= rm.tok_off[r + 1]) break;
+  if (tok < rm.tok_off[r + 1]) {
+    const bool have_prev = step > 0 && hdr[r].has_m;
+    const float* md = mod + (size_t)rm.modrow[r] * ld_mod;
+    const float4* sh = (const float4*)(md + shift_off);
+    const float4* sc = (const float4*)(md + scale_off);
     const float4* xr = (const float4*)(x0 + (size_t)tok * D);
     float4* mr = (float4*)(m_prev + (size_t)tok * D);
-    float4 v[kMaxV4];
+    float4 v[NI], o[NI];
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < kMaxV4; ++i) {
+    for (int i = 0; i < NI; ++i) {
       const int c = lane + 64 * i;
-      if (c < nv) {
-        v[i] = xr[c];
-        s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-      }
+      v[i] = o[i] = float4{0.f, 0.f, 0.f, 0.f};
+      if (c < nv) v[i] = xr[c];
+      if (c < nv && have_prev) o[i] = mr[c];
     }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
     const float mean = wave_sum(s) / (float)D;
     float q = 0.f;
 #pragma unroll
-    for (int i = 0; i < kMaxV4; ++i) {
+    for (int i = 0; i < NI; ++i) {
       const int c = lane + 64 * i;
       if (c < nv) {
         const float a = v[i].x - mean, b = v[i].y - mean, cc = v[i].z - mean, d = v[i].w - mean;
@@ -1239,7 +1244,7 @@ __global__ __launch_bounds__(256) void cache_signal_kernel(
     }
     const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
 #pragma unroll
-    for (int i = 0; i < kMaxV4; ++i) {
+    for (int i = 0; i < NI; ++i) {
       const int c = lane + 64 * i;
       if (c < nv) {
         const float4 a = sh[c], b = sc[c];
@@ -1249,10 +1254,10 @@ __global__ __launch_bounds__(256) void cache_signal_kernel(
         m.z = (v[i].z - mean) * rstd * (1.f + b.z) + a.z;
         m.w = (v[i].w - mean) * rstd * (1.f + b.w) + a.w;
         if (have_prev) {
-          const float4 o = mr[c];
-          num += (double)fabsf(m.x - o.x) + (double)fabsf(m.y - o.y) +
-                 (double)fabsf(m.z - o.z) + (double)fabsf(m.w - o.w);
-          den += (double)fabsf(o.x) + (double)fabsf(o.y) + (double)fabsf(o.z) + (double)fabsf(o.w);
+          num += (double)fabsf(m.x - o[i].x) + (double)fabsf(m.y - o[i].y) +
+                 (double)fabsf(m.z - o[i].z) + (double)fabsf(m.w - o[i].w);
+          den += (double)fabsf(o[i].x) + (double)fabsf(o[i].y) + (double)fabsf(o[i].z) +
+                 (double)fabsf(o[i].w);
         }
         mr[c] = m;
       }
@@ -1265,36 +1270,39 @@ __global__ __launch_bounds__(256) void cache_signal_kernel(
     red[wave][1] = den;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    partial[2 * blockIdx.x + 0] = ((red[0][0] + red[1][0]) + red[2][0]) + red[3][0];
-    partial[2 * blockIdx.x + 1] = ((red[0][1] + red[1][1]) + red[2][1]) + red[3][1];
+  if (threadIdx.x < 2) {
+    double t = 0.0;
+    for (int w = 0; w < kCacheRowsPerBlock; ++w) t += red[w][threadIdx.x];
+    partial[2 * blockIdx.x + threadIdx.x] = t;
   }
 }
 
+// one workgroup of one wave per request
 __global__ void cache_decide_kernel(ReqMap rm, const double* __restrict__ partial,
-                                    CacheHeader* __restrict__ hdr, int step, int n_steps,
+                                    CacheHeader* __restrict__ hdr,
+                                    CacheHeader* __restrict__ host, int step, int n_steps,
                                     double tau, int mode) {
-  const int r = threadIdx.x;
-  if (r >= rm.n) return;
+  const int r = blockIdx.x, lane = threadIdx.x;
   int b0 = 0;
   for (int i = 0; i < r; ++i)
     b0 += (rm.tok_off[i + 1] - rm.tok_off[i] + kCacheRowsPerBlock - 1) / kCacheRowsPerBlock;
   const int nb = (rm.tok_off[r + 1] - rm.tok_off[r] + kCacheRowsPerBlock - 1) / kCacheRowsPerBlock;
   CacheHeader hd = hdr[r];
+  double num = 0.0, den = 0.0;
+  for (int b = lane; b < nb; b += 64) {
+    num += partial[2 * (b0 + b) + 0];
+    den += partial[2 * (b0 + b) + 1];
+  }
+  num = wave_sum(num);
+  den = wave_sum(den);
+  if (lane != 0) return;
   if (step == 0) {
     hd.acc = 0.0;
     hd.has_m = 0;
     hd.has_r = 0;
   }
   double d = __longlong_as_double(0x7ff8000000000000LL);   // NaN: no predecessor
-  if (hd.has_m) {
-    double num = 0.0, den = 0.0;
-    for (int b = 0; b < nb; ++b) {
-      num += partial[2 * (b0 + b) + 0];
-      den += partial[2 * (b0 + b) + 1];
-    }
-    d = num / den;
-  }
+  if (hd.has_m) d = num / den;
   int skip = 0;
   double acc = hd.acc;
   if (tau > 0.0 && step != 0 && step != n_steps - 1 && hd.has_r && hd.has_m) {
@@ -1312,6 +1320,7 @@ __global__ void cache_decide_kernel(ReqMap rm, const double* __restrict__ partia
   hd.skip = skip;
   hd.has_m = 1;
   hdr[r] = hd;
+  host[r] = hd;
 }
 
 hipError_t launch_cache_signal(const float* x0, const ReqMap& rm, const float* mod, int ld_mod,
@@ -1319,15 +1328,19 @@ hipError_t launch_cache_signal(const float* x0, const ReqMap& rm, const float* m
                                CacheHeader* hdr, int step, double* partial, hipStream_t st) {
   const int nb = cache_partial_blocks(rm);
   if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(cache_signal_kernel, dim3(nb), dim3(256), 0, st, x0, rm, mod, ld_mod,
-                     shift_off, scale_off, D, eps, m_prev, hdr, step, partial);
+#define T2I_SIG(NI_)                                                                           \
+  hipLaunchKernelGGL((cache_signal_kernel<NI_>), dim3(nb), dim3(64 * kCacheRowsPerBlock), 0, st, x0, \
+                     rm, mod, ld_mod, shift_off, scale_off, D, eps, m_prev, hdr, step, partial)
+  if (D <= 1280) T2I_SIG(5);
+  else T2I_SIG(kMaxV4);
+#undef T2I_SIG
   return hipGetLastError();
 }
 
 hipError_t launch_cache_decide(const ReqMap& rm, const double* partial, CacheHeader* hdr,
-                               int step, int n_steps, double tau, int mode, hipStream_t st) {
-  hipLaunchKernelGGL(cache_decide_kernel, dim3(1), dim3(64), 0, st, rm, partial, hdr, step,
-                     n_steps, tau, mode);
+                               CacheHeader* host, int step, int n_steps, double tau, int mode, hipStream_t st) {
+  hipLaunchKernelGGL(cache_decide_kernel, dim3(rm.n), dim3(64), 0, st, rm, partial, hdr, host,
+                     step, n_steps, tau, mode);
   return hipGetLastError();
 }
 

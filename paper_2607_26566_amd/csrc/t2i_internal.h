@@ -325,8 +325,10 @@ int cache_partial_blocks(const ReqMap& rm);
 hipError_t launch_cache_signal(const float* x0, const ReqMap& rm, const float* mod, int ld_mod,
                                int shift_off, int scale_off, int D, float eps, float* m_prev,
                                CacheHeader* hdr, int step, double* partial, hipStream_t st);
+// host: page-locked copy of the headers (device-visible)
 hipError_t launch_cache_decide(const ReqMap& rm, const double* partial, CacheHeader* hdr,
-                               int step, int n_steps, double tau, int mode, hipStream_t st);
+                               CacheHeader* host, int step, int n_steps, double tau, int mode,
+                               hipStream_t st);
 // x[b][tok] = x0[tok] + R[b][tok] for requests with skip_mask[r]
 hipError_t launch_apply_residual(const float* x0, const float* R, float* x, const ReqMap& rm,
                                  uint32_t skip_mask, int D, hipStream_t st);
