@@ -101,6 +101,28 @@ __device__ __forceinline__ void decode_tile(const AttnMap& m, int heads, int L, 
   j = t - m.tile_start[s];
 }
 
+// Workgroup b -> (head, sequence, query tile) of a self / joint launch.  The
+// sequences with the most keys go first, so that a launch of unequal sequences
+// does not end on its longest workgroups.  Workgroups are dealt to the XCDs in
+// turn: XCD x takes the heads x, x + 8, .. (all tiles of a head and sequence on
+// one XCD, so that they share K / V in its L2), its own workgroups in the same
+// order of sequences.
+__device__ __forceinline__ void decode_ordered(const AttnMap& m, int heads, int b, int& h, int& s,
+                                               int& j) {
+  const int per = heads >> 3;
+  int r = b >> 3, i = 0, nt;
+#pragma unroll 1
+  for (;; ++i) {
+    s = m.order[i];
+    nt = m.tile_start[s + 1] - m.tile_start[s];
+    if (r < per * nt || i + 1 >= m.n) break;
+    r -= per * nt;
+  }
+  const int q = r / nt;
+  h = (b & 7) + 8 * q;
+  j = r - q * nt;
+}
+
 // ROLE: 0 = self / joint attention, 1 = cross-attention to text (separate
 // instances, so that profiles tell them apart).  QS: Q arrives already
 // multiplied by scale_log2 (the model's projections write it so, rounding the
@@ -140,8 +162,21 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_bf16_kernel(AttnMap map,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int hh, s, j;
-  decode_tile<ROLE == 1>(map, heads, xcd_remap_attn(blockIdx.x, gridDim.x), hh, s, j);
-  const int q_beg = map.q_start[s], q_end = q_beg + map.q_len[s];
+  constexpr bool ARRANGED = ROLE == 0 && NW > 2;   // (attention_tiles leaves 2-wave launches as they come)
+  if (ARRANGED && map.ordered && heads % 8 == 0)
+    decode_ordered(map, heads, blockIdx.x, hh, s, j);
+  else
+    decode_tile<ROLE == 1>(map, heads, xcd_remap_attn(blockIdx.x, gridDim.x), hh, s, j);
+  // this wave's 32 queries, from the sequence's first or second run
+  int grp = j * NW + wave;
+  bool run2 = false;
+  if constexpr (ARRANGED) {
+    const int g1 = (map.q_len[s] + 31) >> 5;
+    run2 = grp >= g1;
+    if (run2) grp -= g1;
+  }
+  const int q_beg = run2 ? map.q2_start[s] : map.q_start[s];
+  const int q_end = q_beg + (run2 ? map.q2_len[s] : map.q_len[s]);
   // key tiles: those of segment 1, then those of segment 2
   const int k1 = map.k_start[s], n1 = map.k_len[s];
   const int k2 = map.k2_start[s], n2 = map.k2_len[s];
@@ -156,7 +191,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_bf16_kernel(AttnMap map,
   // 32x32x16 MFMA lane roles: column (query) ql, k-half hl; C element 4i + jj
   // of a lane is row 8i + 4hl + jj
   const int ql = lane & 31, hl = lane >> 5;
-  const int qr = q_beg + j * BQ + wave * 32 + ql;
+  const int qr = q_beg + grp * 32 + ql;
   auto kst = [&](int st) { return smem + st * (KSTAGE + VSTAGE); };
   auto vst = [&](int st) { return smem + st * (KSTAGE + VSTAGE) + KSTAGE; };
 
@@ -873,11 +908,14 @@ constexpr int attn_stages() {
 }
 constexpr int kCrossWaves = 4, kCrossStages = 3;
 void attention_tiles(AttnMap& m, bool bf16_io, int heads, int role) {
+  for (int s = 0; s < m.n; ++s) m.q2_start[s] = m.q2_len[s] = 0;
+  m.ordered = 0;
   auto fill = [&](int bq) {
     int t = 0;
     for (int s = 0; s < m.n; ++s) {
       m.tile_start[s] = t;
-      t += (m.q_len[s] + bq - 1) / bq;
+      t += m.q2_len[s] ? ((m.q_len[s] + 31) / 32 + (m.q2_len[s] + 31) / 32 + bq / 32 - 1) / (bq / 32)
+                       : (m.q_len[s] + bq - 1) / bq;
     }
     m.tile_start[m.n] = t;
     return (long)t * heads;
@@ -887,6 +925,71 @@ void attention_tiles(AttnMap& m, bool bf16_io, int heads, int role) {
     fill(64);
     return;
   }
+  auto merge_runs = [&]() {
+    // Neighbouring sequences with the same keys become one of two runs: 77 text
+    // and 2451 image queries take 10 tiles of 256 instead of 11 (24 heads of
+    // them then fit one round of 256 workgroups).
+    int n = 0;
+    for (int s = 0; s < m.n; ++s) {
+      if (n > 0 && m.q2_len[n - 1] == 0 && m.q_len[n - 1] > 0 && m.q_len[s] > 0 &&
+          m.k_start[n - 1] == m.k_start[s] && m.k_len[n - 1] == m.k_len[s] &&
+          m.k2_start[n - 1] == m.k2_start[s] && m.k2_len[n - 1] == m.k2_len[s]) {
+        m.q2_start[n - 1] = m.q_start[s];
+        m.q2_len[n - 1] = m.q_len[s];
+        continue;
+      }
+      m.q_start[n] = m.q_start[s];
+      m.q_len[n] = m.q_len[s];
+      m.k_start[n] = m.k_start[s];
+      m.k_len[n] = m.k_len[s];
+      m.k2_start[n] = m.k2_start[s];
+      m.k2_len[n] = m.k2_len[s];
+      ++n;
+    }
+    m.n = n;
+  };
+  // Longest sequences first, where that ends the launch earlier: the jobs of
+  // one XCD (its share of the heads, decode_ordered), each its keys and a fixed
+  // cost worth about 500, dealt in either order to its 32 CUs: one job per CU
+  // (two where a CU takes two workgroups of 4 waves), then the least loaded CU
+  // next.
+  auto order = [&](int waves) {
+    const int n = m.n;
+    auto keys = [&](int s) { return (long)m.k_len[s] + m.k2_len[s]; };
+    bool alike = true;
+    for (int s = 0; s < n; ++s) {
+      m.order[s] = s;
+      alike = alike && keys(s) == keys(0);
+    }
+    if (alike || heads % 8) return;
+    std::stable_sort(m.order, m.order + n, [&](int a, int b) { return keys(a) > keys(b); });
+    auto makespan = [&](bool sorted) {
+      constexpr int slots = 32;
+      const int first = waves == kAttnWaves ? slots : 2 * slots;
+      long busy[slots] = {};   // a min-heap of the CUs' loads once the first jobs are dealt
+      int dealt = 0;
+      auto later = [](long a, long b) { return a > b; };
+      auto deal = [&](int s, int jobs) {
+        for (int i = 0; i < jobs; ++i, ++dealt) {
+          if (dealt < first) {
+            busy[dealt % slots] += keys(s) + 500;
+            continue;
+          }
+          if (dealt == first) std::make_heap(busy, busy + slots, later);
+          std::pop_heap(busy, busy + slots, later);
+          busy[slots - 1] += keys(s) + 500;
+          std::push_heap(busy, busy + slots, later);
+        }
+      };
+      for (int h = 0; h < (sorted ? 1 : heads / 8); ++h)
+        for (int i = 0; i < n; ++i) {
+          const int s = sorted ? m.order[i] : i;
+          deal(s, (m.tile_start[s + 1] - m.tile_start[s]) * (sorted ? heads / 8 : 1));
+        }
+      return *std::max_element(busy, busy + slots);
+    };
+    m.ordered = makespan(true) * 100 < makespan(false) * 97;
+  };
   // default workgroup size; self / joint attention halves it while the
   // launch has fewer workgroups than CUs (256 on MI355X) -- cross-attention,
   // with two key tiles per query tile, measured slower with smaller groups
@@ -895,6 +998,18 @@ void attention_tiles(AttnMap& m, bool bf16_io, int heads, int role) {
   while (role == 0 && w > 2 && wgs < 256) {
     w /= 2;
     wgs = fill(32 * w);
+  }
+  // The launches of larger workgroups are arranged for their ends: runs merged,
+  // longest sequences first (24 heads of 77 + 2451 and 77 + 1037 joint queries
+  // 168 -> 135 us, 16 heads of 3952 + 2640 + 1024 + 432 + 120 139 -> 132, of
+  // 120 + 1700 and 120 + 900 38.0 -> 29.9; 3 x 256 + 3 x 1024 + 2 x 4096, whose
+  // end would be the same, keep their order: sorted 200 -> 204).  Those of
+  // 2-wave workgroups are one short round, where the few extra scalar loads
+  // cost more (1024 queries 21.6 -> 22.3 us).
+  if (role == 0 && w > 2) {
+    merge_runs();
+    fill(32 * w);
+    order(w);
   }
   m.waves = w;
 }

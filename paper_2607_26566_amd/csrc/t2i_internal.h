@@ -39,6 +39,14 @@ struct AttnMap {
   int q_start[kMaxSeq], q_len[kMaxSeq], k_start[kMaxSeq], k_len[kMaxSeq];
   int k2_start[kMaxSeq], k2_len[kMaxSeq];
   int tile_start[kMaxSeq + 1];
+  // Set by attention_tiles for self / joint attention.  A second run of query
+  // rows with the same keys (joint attention: a request's text rows and its
+  // image rows): its 32-query groups follow the first run's, so that a
+  // workgroup may hold groups of both.
+  int q2_start[kMaxSeq], q2_len[kMaxSeq];
+  // sequences by key count, most keys first; used where `ordered`
+  int ordered;
+  int order[kMaxSeq];
 };
 
 // Cross-attention fused into its query projection (gemm_dma_kernel with XAttnArgs): the
