@@ -508,3 +508,47 @@ def test_packed_mixed_skip_runs_blocks_on_computing_requests_only(packed8):
             assert np.array_equal(v_mix[r], v_ref[r]), (mixed, r)
             assert np.array_equal(x_mix[r], x_ref[r]), (mixed, r)
         say(f"mixed skip {mixed}: computing and skipped requests bitwise as in the uniform steps")
+
+
+# (changes to the tiny fp32 model): patch widths of 16, 64 (one and two guidance
+# branches) and neither, token counts off the 16-token tiles, rows of 1152 and
+# fewer, and more, columns
+EDGE_MODELS = [
+    dict(latent_channels=4, requests=((6, 14), (2, 2)), guidance=3.0),
+    dict(latent_channels=16, requests=((10, 6), (2, 14))),
+    dict(latent_channels=16, requests=((10, 6),), guidance=3.0),
+    dict(latent_channels=3, requests=((6, 10),), guidance=2.0),
+    dict(latent_channels=4, requests=((6, 6),), hidden=1344, heads=21, mlp_hidden=64, guidance=2.0),
+    dict(latent_channels=16, requests=((34, 2),), hidden=64, heads=1, mlp_hidden=64),
+]
+
+
+@pytest.mark.parametrize("changes", EDGE_MODELS, ids=range(len(EDGE_MODELS)))
+def test_embedding_final_layer_and_signal_edges(changes):
+    """One fp32 step and two cache checks of small models against the oracle."""
+    w = synth.reduced(synth.workload("tiny_f32"), depth=1, steps=4, **changes)
+    M = Model(w)
+    lats, texts = synth.latents(w), synth.texts(w)
+    hw, R = list(w.requests), w.n_req
+    t, tn = [0.9 - 0.2 * r for r in range(R)], [0.8 - 0.2 * r for r in range(R)]
+    x, tx = M.latents_dev(lats), M.text_dev(texts)
+    v = torch.zeros_like(x)
+    t2i.t2i_dit_step(M.m, x, hw, t, tx, guidance=w.guidance, t_next=tn, noise_pred=v)
+    torch.cuda.synchronize()
+    new, vs, _, _, _ = sampler.step(M.W, w, lats, texts, t, tn, w.guidance)
+    err = rel_l2(v.cpu().numpy(), np.concatenate([a.ravel() for a in vs]))
+    say(f"edge model {changes}: rel_l2 {err:.2e}")
+    assert err < 1e-5      # fp32 sums of at most 1344 terms through one block
+    assert rel_l2(x.cpu().numpy(), np.concatenate([a.ravel() for a in new])) < 1e-6
+    cs = M.m.new_cache_state(w_tokens(w), w.branches)
+    args = dict(n_steps=4, tau=0.1, cache_state=cs, branches=w.branches)
+    t2i.t2i_cache_check(M.m, M.latents_dev(lats), hw, t, 0, **args)
+    rel, _ = t2i.t2i_cache_check(M.m, x, hw, tn, 1, **args)
+    for r in range(R):
+        ref = sampler.rel_l1(dit.cache_signal(M.W, w, new[r], tn[r]).astype(np.float32),
+                             dit.cache_signal(M.W, w, lats[r], t[r]).astype(np.float32))
+        assert abs(rel[r] - ref) < 1e-4 * ref
+
+
+def w_tokens(w):
+    return [w.tokens(r) for r in range(w.n_req)]

@@ -149,6 +149,43 @@ def test_linear_bf16_operand_over_2gib():
     torch.cuda.empty_cache()
 
 
+# one shape per tile of the direct-load GEMM (rows x columns of the tile it
+# takes), rows not a multiple of the tile's
+DMA_TILE_SHAPES = [(17, 1152, "32x64"), (33, 9216, "32x128"), (100, 9216, "32x144"),
+                   (65, 12288, "64x128"), (900, 2304, "64x144"), (130, 12288, "128x128"),
+                   (900, 4608, "128x144"), (333, 12288, "128x192"), (1000, 4608, "256x128"),
+                   (700, 9216, "256x144"), (700, 12288, "256x192"), (4097, 3072, "256x256"),
+                   (1410, 9216, "256x288")]
+
+
+@pytest.mark.parametrize("K", [64, 192])
+@pytest.mark.parametrize("M,N,tile", DMA_TILE_SHAPES, ids=[t[2] for t in DMA_TILE_SHAPES])
+def test_linear_bf16_every_tile(M, N, tile, K):
+    """Every tile of the direct-load GEMM at one K step and at an odd number of
+    steps: sampled rows against float64, and the first and last rows computed
+    alone (the 32-row tile) bitwise the same, for each kind of epilogue."""
+    say(f"linear bf16 {M}x{N}x{K} ({tile})")
+    A, W, b = rnd(90, (M, K)), rnd(91, (N, K), 0.05), rnd(92, (N,), 0.1)
+    x0, gate = rnd(93, (M, N), bf=False), rnd(94, (N,), 0.5, bf=False)
+    rows = np.unique(np.r_[0, M // 2, M - 1])
+    ref = dit.linear(A[rows].astype(np.float64), W.astype(np.float64), b.astype(np.float64))
+    tail = slice(max(0, M - 30), M)
+    for epi, f in ((_lib.T2I_EPI_STORE, lambda y: y), (_lib.T2I_EPI_GELU, dit.gelu_tanh),
+                   (_lib.T2I_EPI_SILU, dit.silu)):
+        out, _, _ = run_linear(_lib.T2I_BF16, epi, A, W, b)
+        assert rel_l2(to_host(out[torch.from_numpy(rows).to(DEV)]), f(ref)) < 3e-3   # one bf16 rounding
+        few, _, _ = run_linear(_lib.T2I_BF16, epi, A[tail], W, b)
+        assert torch.equal(few, out[tail])
+    _, x, xc = run_linear(_lib.T2I_BF16, _lib.T2I_EPI_RESID_GATED, A, W, b, resid=x0, gate=gate,
+                          with_copy=True)
+    got = x.cpu().numpy()
+    assert rel_l2(got[rows].astype(np.float64) - x0[rows], gate * ref) < 1e-4
+    assert np.array_equal(xc.float().cpu().numpy(), synth.round_bf16(got))
+    _, few, _ = run_linear(_lib.T2I_BF16, _lib.T2I_EPI_RESID_GATED, A[tail], W, b, resid=x0[tail],
+                           gate=gate)
+    assert torch.equal(few, x[tail])
+
+
 @pytest.mark.parametrize("M,N,K,epi", [(64, 128, 256, 0), (100, 520, 128, 2), (77, 33, 90, 4)])
 def test_linear_f32(M, N, K, epi):
     A, W, b = rnd(10, (M, K), bf=False), rnd(11, (N, K), 0.05, bf=False), rnd(12, (N,), 0.1, bf=False)
@@ -680,3 +717,60 @@ def test_lora_merge_batch_equals_single_merges(dtype, n_out, n_in, rank):
     torch.cuda.synchronize()
     for x, y in zip(one, bat):
         assert torch.equal(x, y)
+
+
+# (heads, head size, text keys, image lengths): launches of 8- and 4-wave
+# workgroups whose text and image queries share workgroups and whose longest
+# sequences go first; equal lengths; heads that are no multiple of 8
+ARRANGED = [(24, 128, 77, [1301, 437]), (16, 72, 40, [1500, 900]), (8, 64, 0, [2100, 333, 64]),
+            (16, 72, 24, [1200, 1200]), (12, 72, 33, [1500, 700])]
+
+
+@pytest.mark.parametrize("H,d,text,lens", ARRANGED)
+def test_attention_bf16_arranged_launches(H, d, text, lens):
+    """Joint sequences of unequal length: sampled rows against float64, and
+    every sequence bitwise what it is alone."""
+    say(f"attention bf16 arranged {H}x{d} text {text} lens {lens}")
+    w, row, seqs, seg2 = H * d, 0, [], []
+    for n in lens:
+        img = row + (text + 7) // 8 * 8
+        if text:
+            seqs += [(row, text, row, text), (img, n, row, text)]
+            seg2 += [(img, n)] * 2
+        else:
+            seqs.append((img, n, img, n))
+        row = img + (n + 7) // 8 * 8
+    q, k, v = (rnd(110 + i, (row, w)) for i in range(3))
+    got = run_attention(_lib.T2I_BF16, H, d, seqs, q, k, v, seg2 or None)
+    for i, (q0, nq, k0, nk) in enumerate(seqs):
+        alone = run_attention(_lib.T2I_BF16, H, d, [seqs[i]], q, k, v, [seg2[i]] if seg2 else None)
+        assert np.array_equal(got[q0:q0 + nq], alone[q0:q0 + nq])
+        kk, vv = k[k0:k0 + nk], v[k0:k0 + nk]
+        if seg2:
+            kk = np.concatenate([kk, k[seg2[i][0]:sum(seg2[i])]])
+            vv = np.concatenate([vv, v[seg2[i][0]:sum(seg2[i])]])
+        rows = np.unique(np.r_[q0, q0 + nq // 2, q0 + nq - 1])
+        ref = dit.attention(q[rows].astype(np.float64), kk.astype(np.float64), vv.astype(np.float64), H)
+        assert rel_l2(got[rows], ref) < 6e-3
+
+
+@pytest.mark.parametrize("n,n_out,n_in,rank", [(1, 2600, 264, 7), (40, 400, 1160, 3), (2, 1, 8, 1),
+                                               (20, 1030, 1152, 100), (1, 33, 72, 127)])
+def test_lora_merge_strips(n, n_out, n_in, rank):
+    """Row steps per wave, ranks that are no multiple of 8, edges of rows and columns."""
+    from oracle import lora
+    Ws = [rnd(120, (n_out, n_in), 0.05), rnd(121, (n_out, n_in), 0.05)]
+    As = [rnd(122, (rank, n_in), 0.05), rnd(123, (rank, n_in), 0.05)]
+    Bs = [rnd(124, (n_out, rank), 0.05), rnd(125, (n_out, rank), 0.05)]
+    dW = [to_dev(Ws[i % 2], "bf16") for i in range(n)]
+    dA = [to_dev(As[i % 2], "bf16") for i in range(n)]
+    dB = [to_dev(Bs[i % 2], "bf16") for i in range(n)]
+    t2i.lora_merge_batch(dW, dA, dB, 0.7)
+    torch.cuda.synchronize()
+    for i in (0, 1) if n > 1 else (0,):
+        ref = lora.merge(Ws[i], As[i], Bs[i], 0.7)
+        got = to_host(dW[i])
+        # one rounding to bf16 of an fp32 sum: half a step, and the sum's own error
+        assert np.all(np.abs(got - ref) <= np.maximum(np.abs(ref), np.abs(got)) * 2.0 ** -8 + 1e-6)
+    for i in range(2, n):
+        assert torch.equal(dW[i], dW[i % 2])
