@@ -541,9 +541,9 @@ hipError_t launch_gemm_bf16_group(const bf16* A, int lda, const PtrGroup& g, int
 // fp32 GEMM on the fp32 matrix cores (v_mfma_f32_16x16x4_f32: fp32 products,
 // fp32 accumulation), for the fp32 model's layers.  Bound by the matrix cores
 // (157 TFLOP/s fp32) at the model's 1024 rows and by load latency at the
-// smallest (64 rows).  1024 x 4608 x 1152 takes 112 us (97 TFLOP/s) where
-// vector FMAs took 213, 1024 x 1152 x 4608 128 against 620, and 64 x 128 x 512
-// 6.8 against 62.
+// smallest (64 rows).  1024 x 4608 x 1152 takes 91 us (119 TFLOP/s)
+// where vector FMAs took 213, 1024 x 1152 x 4608 114 against 620, and 64 x 128
+// x 512 6.8 against 62.
 //
 // 4 waves as 2 x 2 own a (32 TM) x (32 TN) tile.  K advances 32 floats (128
 // bytes, 8 chunks of 16) at a time through a ring of four LDS stages filled by
@@ -921,7 +921,7 @@ hipError_t launch_gemm_f32(const float* A, int lda, const float* W, int ldw, con
   // 256 per 32 x 32 of the tile) and their loads at ~20 bytes per clock.
   auto cost = [&](long bm, long bn) {
     const long tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    return ((tiles + 255) / 256) * std::max(bm * bn / 4, (bm + bn) * 128 / 20);
+    return ((tiles + 255) / 256) * std::max(bm * bn / 4, (bm + bn) * 128 / 32);
   };
   const long c22 = cost(64, 64), c12 = cost(32, 64), c11 = cost(32, 32);
   if (c22 <= c12 && c22 <= c11)
