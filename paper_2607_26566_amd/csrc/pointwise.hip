@@ -886,11 +886,11 @@ hipError_t launch_bias_rows_f32(const void* bias, bool bias_bf16, int rows, int 
 // the modulated rows to LDS, CH columns at a time; the waves then share the
 // contraction of those columns: wave w takes the 32-column steps w, w + 8, ...
 // for all tokens, branches and outputs on v_mfma_f32_16x16x4_f32 (fp32 rows
-// against the weights widened to fp32).  The waves' sums are added in wave
+// against the weights widened to fp32).  The waves' sums are added in a fixed
 // order.  Bound by reading the rows (and, at P = 64, the projection once per
 // 16 tokens from L2).  Against one wave per token (P = 16) or a 32-token
-// register tile (P = 64) on vector FMAs: 28.4 -> 19.2 us at 4096 tokens x 2
-// branches and 37.4 -> 18.7 at 8168 x 1 (width 1152), 220 -> 44 at 4096 tokens
+// register tile (P = 64) on vector FMAs: 28.4 -> 19.3 us at 4096 tokens x 2
+// branches and 37.4 -> 20.2 at 8168 x 1 (width 1152), 220 -> 44 at 4096 tokens
 // of width 3072; 13 us either way at 1024 tokens.
 
 template <typename TW>
@@ -978,11 +978,16 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
   for (int i = 0; i < 2; ++i)
     md[i] = mod + (size_t)rm.modrow[req_of_token(rm, min(tok0 + 2 * wave + i, T - 1))] * ld_mod;
 
-  f32x4 acc[NB][NT];
+  // NA sums per output (16 outputs: four, a quarter of the terms each: shorter
+  // chains of additions, so less rounding, and four independent MFMA chains)
+  constexpr int NA = NT == 1 ? 4 : 1;
+  f32x4 acc[NB][NT][NA];
 #pragma unroll
   for (int br = 0; br < NB; ++br)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) acc[br][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) acc[br][j][a] = f32x4{0.f, 0.f, 0.f, 0.f};
   constexpr int NCH = CH % 256 ? 1 : NI * 256 / CH;   // (whole rows when CH is no multiple of 256)
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
@@ -1027,7 +1032,8 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
         for (int e = 0; e < 8; ++e)
 #pragma unroll
           for (int j = 0; j < NT; ++j)
-            acc[br][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][e], h[e], acc[br][j], 0, 0, 0);
+            acc[br][j][e % NA] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][e], h[e], acc[br][j][e % NA], 0, 0, 0);
       }
     }
   }
@@ -1035,7 +1041,10 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
 #pragma unroll
   for (int br = 0; br < NB; ++br)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) part[((wave * NB + br) * NT + j) * 64 + lane] = acc[br][j];
+    for (int j = 0; j < NT; ++j)
+      part[((wave * NB + br) * NT + j) * 64 + lane] =
+          NA == 4 ? (acc[br][j][0] + acc[br][j][1 % NA]) + (acc[br][j][2 % NA] + acc[br][j][3 % NA])
+                  : acc[br][j][0];
   __syncthreads();
   // lane: token fr, outputs 16 j + 4 g .. + 3
   const int tok = tok0 + fr;
@@ -1046,9 +1055,11 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
     y[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int br = 0; br < NB; ++br) {
-      y[br] = part[(br * NT + j) * 64 + lane];
+      // the eight waves' sums, in pairs
+      f32x4 s[8];
 #pragma unroll
-      for (int q = 1; q < 8; ++q) y[br] += part[((q * NB + br) * NT + j) * 64 + lane];
+      for (int q = 0; q < 8; ++q) s[q] = part[((q * NB + br) * NT + j) * 64 + lane];
+      y[br] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
