@@ -234,12 +234,50 @@ hipError_t launch_ln_modulate(bool bf16_out, int rows, int D, const float* x, in
 
 // embed_mfma_kernel (P a multiple of 16): a workgroup takes 16 tokens x 16 ET
 // channels per wave on v_mfma_f32_16x16x4_f32 (fp32 patches, weights widened to
-// fp32).  The patches are gathered into LDS once and kept in registers as the
-// token operand; with the weights as the row operand a lane ends with four
-// consecutive channels of one token; the tile leaves along the rows.  Bound by the stores:
+// fp32).  That instruction is a chain of four fused multiply-adds, lane group 0
+// first, so with MFMA m of a 16-feature chunk taking features 4 m + g every
+// channel is its bias plus the products in ascending order, bit for bit what
+// embed_kernel computes.  The patches are gathered into LDS once and kept in
+// registers as the token operand; with the weights as the row operand a lane
+// ends with four consecutive channels of one token; the tile leaves along the
+// rows.  Bound by the stores:
 // 14 us at 4096 tokens x 2 branches of width 1152 (one channel per thread with
 // the patches read from LDS: 16.6), 48 at 4096 tokens of width 3072 (53).
 // embed_kernel: any other P <= 64, one channel per thread.
+
+// Four consecutive values per lane -> o[m] of lane group g (lanes 16 g .. 16 g +
+// 15) = value g of lane group m, in fp32: the two lane bits trade places with
+// the two index bits (bf16: the upper index bit while two values share a
+// register).
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(p[0]);
+  b = __uint_as_float(p[1]);
+}
+__device__ __forceinline__ void transpose_groups(bf16x4 q, float (&o)[4]) {
+  union {
+    bf16x4 v;
+    uint32_t u[2];
+  } x = {q};
+  const auto p = __builtin_amdgcn_permlane32_swap(x.u[0], x.u[1], false, false);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    o[2 * h] = __uint_as_float(p[h] << 16);
+    o[2 * h + 1] = __uint_as_float(p[h] & 0xffff0000u);
+    swap16(o[2 * h], o[2 * h + 1]);
+  }
+}
+__device__ __forceinline__ void transpose_groups(f32x4 q, float (&o)[4]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(q[h]), __float_as_uint(q[2 + h]),
+                                                    false, false);
+    o[h] = __uint_as_float(p[0]);
+    o[2 + h] = __uint_as_float(p[1]);
+  }
+  swap16(o[0], o[1]);
+  swap16(o[2], o[3]);
+}
 
 // the 16-token patch gather both kernels start with: patch[t][(a p + b) C + c],
 // and each token's grid position
@@ -304,30 +342,24 @@ __global__ __launch_bounds__(256) void embed_mfma_kernel(const float* __restrict
   const int qd = D / 4, d00 = (blockIdx.x * 4 + wave) * ET * 16;
   // the wave's weights and biases, fetched while the patches are gathered
   // (channel tiles past D repeat the last one and are not stored)
-  float w[ET][KC][4], add[ET][4];
+  typedef TW tw4 __attribute__((ext_vector_type(4)));
+  tw4 w[ET][KC];
+  float add[ET][4];
 #pragma unroll
   for (int j = 0; j < ET; ++j) {
     const int d0 = min(d00 + j * 16, D - 16);
     const TW* wr = w_pe + (size_t)(d0 + fr) * P + 4 * g;
 #pragma unroll
-    for (int c = 0; c < KC; ++c) {
-      if constexpr (sizeof(TW) == 2) {
-        const bf16x4 q = *(const bf16x4*)(wr + 16 * c);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[j][c][e] = (float)q[e];
-      } else {
-        const f32x4 q = *(const f32x4*)(wr + 16 * c);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[j][c][e] = q[e];
-      }
-    }
+    for (int c = 0; c < KC; ++c) w[j][c] = *(const tw4*)(wr + 16 * c);
 #pragma unroll
     for (int e = 0; e < 4; ++e) add[j][e] = to_f32(b_pe[d0 + 4 * g + e]);
   }
   gather_patches(es, lat, rm, t0, P, C, p);
-  f32x4 pf[KC];
+  float pf[KC][4];
 #pragma unroll
-  for (int c = 0; c < KC; ++c) pf[c] = *(const f32x4*)&es.patch[fr][16 * c + 4 * g];
+  for (int c = 0; c < KC; ++c)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) pf[c][m] = es.patch[fr][16 * c + 4 * m + g];
   float pos[ET][4];
   if (pe) {
     // D / 4 is a multiple of 16: a lane's four channels lie in one of the four
@@ -352,16 +384,18 @@ __global__ __launch_bounds__(256) void embed_mfma_kernel(const float* __restrict
   float* const sw = stage[wave];
 #pragma unroll
   for (int j = 0; j < ET; ++j) {
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 acc = f32x4{add[j][0], add[j][1], add[j][2], add[j][3]};
 #pragma unroll
-    for (int c = 0; c < KC; ++c)
+    for (int c = 0; c < KC; ++c) {
+      float wt[4];
+      transpose_groups(w[j][c], wt);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][c][e], pf[c][e], acc, 0, 0, 0);
+      for (int m = 0; m < 4; ++m)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[m], pf[c][m], acc, 0, 0, 0);
+    }
+    if (pe) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[e] += add[j][e];
-      if (pe) acc[e] += pos[j][e];
+      for (int e = 0; e < 4; ++e) acc[e] += pos[j][e];
     }
     *(f32x4*)&sw[fr * SP + j * 16 + 4 * g] = acc;
   }

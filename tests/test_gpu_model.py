@@ -552,3 +552,48 @@ def test_embedding_final_layer_and_signal_edges(changes):
 
 def w_tokens(w):
     return [w.tokens(r) for r in range(w.n_req)]
+
+
+def fma(a, b, c):
+    """fp32 fused multiply-add: the product is exact in 64 mantissa bits, and so
+    (but for ties 2^-40 apart) is the sum's one rounding."""
+    return (np.longdouble(a) * np.longdouble(b) + np.longdouble(c)).astype(np.float32)
+
+
+# (changes to a workload): patch widths of 16 and 64 in both types, with and
+# without position embedding, a token count off the 16-token tiles, widths off
+# the 384 channels of a workgroup
+EMBED_ORDER = [
+    ("tiny_f32", dict(latent_channels=4, requests=((6, 14),))),
+    ("tiny_f32", dict(latent_channels=16, requests=((10, 6),), hidden=1344, heads=21, mlp_hidden=64)),
+    ("tiny_f32", dict(latent_channels=3, requests=((6, 10),))),
+    ("dit512", dict(requests=((8, 20),), mlp_hidden=64, text_dim=64)),
+    ("mmdit1024", dict(requests=((8, 12),), hidden=256, heads=2, mlp_hidden=64, text_dim=64)),
+]
+
+
+@pytest.mark.parametrize("name,changes", EMBED_ORDER)
+def test_embedding_adds_in_feature_order(name, changes):
+    """Every channel of the embedding is its bias plus the patch products in
+    ascending feature order, fused, then the position: bitwise, whichever
+    kernel runs."""
+    w = synth.reduced(synth.workload(name), depth=1, steps=1, guidance=1.0, **changes)
+    M = Model(w)
+    lats = synth.latents(w)
+    (h, wd), C, D = w.requests[0], w.latent_channels, w.hidden
+    T = w.tokens(0)
+    hid = torch.zeros((T + (w.text_tokens if w.arch == "mmdit" else 0), D), device=DEV)
+    step_gpu(M, M.latents_dev(lats), [(h, wd)], [0.5], M.text_dev(synth.texts(w)), n_blocks=0,
+             hidden_out=hid)
+    names = [n for n, _ in t2i.weight_table(M.cfg)]
+    wp, b = (M.host[names.index("x_embed." + n)].astype(np.float32) for n in "wb")
+    p = lats[0].astype(np.float32).reshape(C, h // 2, 2, wd // 2, 2).transpose(1, 3, 2, 4, 0).reshape(T, -1)
+    x = np.repeat(b.reshape(1, D), T, 0)
+    for k in range(p.shape[1]):
+        x = fma(wp.reshape(D, -1)[None, :, k], p[:, k, None], x)
+    if w.arch != "mmdit":
+        om = 10000.0 ** (-np.arange(D // 4) / (D // 4))
+        i, j = np.divmod(np.arange(T), wd // 2)
+        x = x + np.concatenate([f(q[:, None] * om) for q in (i, j) for f in (np.sin, np.cos)],
+                               1).astype(np.float32)
+    assert np.array_equal(hid[:T].cpu().numpy(), x)
