@@ -917,28 +917,26 @@ hipError_t launch_bias_rows_f32(const void* bias, bool bias_bf16, int rows, int 
 // final_mfma_kernel (P = 16 or 64): a workgroup of 8 waves takes 16 tokens in
 // all NB guidance branches.  A wave holds 2 NB rows in registers (one
 // coalesced read), takes their LayerNorm statistics in two passes, and writes
-// the modulated rows to LDS, CH columns at a time; the waves then share the
-// contraction of those columns: wave w takes the 32-column steps w, w + 8, ...
-// for all tokens, branches and outputs on v_mfma_f32_16x16x4_f32 (fp32 rows
-// against the weights widened to fp32).  The waves' sums are added in a fixed
-// order.  Bound by reading the rows (and, at P = 64, the projection once per
-// 16 tokens from L2).  Against one wave per token (P = 16) or a 32-token
-// register tile (P = 64) on vector FMAs: 28.4 -> 19.3 us at 4096 tokens x 2
-// branches and 37.4 -> 20.2 at 8168 x 1 (width 1152), 220 -> 44 at 4096 tokens
-// of width 3072; 13 us either way at 1024 tokens.
-
-template <typename TW>
-__device__ __forceinline__ void ld_w8(const TW* w, float (&o)[8]) {
-  if constexpr (sizeof(TW) == 2) {
-    const bf16x8 q = *(const bf16x8*)w;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (float)q[e];
-  } else {
-    const float4 a = *(const float4*)w, b = *(const float4*)(w + 4);
-    o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
-    o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
-  }
-}
+// the modulated rows to LDS, CH columns at a time; the contraction runs on
+// v_mfma_f32_16x16x4_f32 (fp32 rows against the weights widened to fp32),
+// which is a chain of four fused multiply-adds.  A lane loads
+// eight consecutive weights of its output and trades them between the lane
+// groups, so that an MFMA takes four consecutive columns, and the sums are
+// those of final_kernel, bit for bit:
+//  * CHAINS: columns 256 i + 4 l .. + 3 belong to chain l of 64, as to lane l
+//    there; wave w runs the chains 8 w + n (n = 0 .. 7) side by side, MFMA n of
+//    its 32 columns of every 256, and the 64 are added in the pairs of wave_sum.
+//  * otherwise one chain over all columns, ascending (P = 64 in bf16, where a
+//    wave per token would read the projection once per token): wave w takes
+//    outputs 16 (w % 4) .. of branch w / 4, 32 columns a step, and the next
+//    part of the rows is written to LDS before a part is contracted.
+// Bound by reading the rows and, at P = 64, by the one chain (768 dependent
+// MFMAs, 10 us) and the projection read once per 16 tokens from L2.  Against
+// one wave per token (P = 16) or a 32-token register tile (P = 64) on vector
+// FMAs: 28.4 -> 20.9 us at 4096 tokens x 2 branches and 37.4 -> 21.7 at 8168 x 1
+// (width 1152), 220 -> 51 at 4096 tokens of width 3072; 13 us either way at 1024
+// tokens.  Sums in an order of their own, without the exchange of the 64 chains
+// or the one chain, took 20.0, 19.6 and 46 us.
 
 // v = v_u + g (v_c - v_u) into output f of token `tok` (request r): unpatchify,
 // noise_pred, Euler update
@@ -956,9 +954,9 @@ __device__ __forceinline__ void final_store(const ReqMap& rm, int tok, int r, in
   if (dt != 0.f) lat[li] = lat[li] + dt * vel;
 }
 
-// NT: P / 16; NI: float4 per lane and row (D <= 256 NI); CH: columns in LDS at
-// a time (a multiple of 256, or all of them)
-template <typename TW, int NT, int NI, int CH, int NB>
+// NI: float4 per lane and row (D <= 256 NI); CH: columns in LDS at a time (a
+// multiple of 256, or all of them)
+template <typename TW, int NI, int CH, int NB, bool CHAINS>
 __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict__ x, ReqMap rm,
                                                          const TW* __restrict__ w_out,
                                                          const TW* __restrict__ b_out,
@@ -968,10 +966,11 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
                                                          float* __restrict__ lat,
                                                          float* __restrict__ noise_pred) {
   constexpr int NR = 2 * NB, P = CH + 4;   // rows per wave; LDS row pitch
-  constexpr int ROWS = NB * 16 * P * 4, PART = 8 * NB * NT * 64 * 16;
+  constexpr int BUFS = CHAINS ? 1 : 2;
+  constexpr int ROWS = BUFS * NB * 16 * P * 4, PART = (CHAINS ? 64 : 4) * NB * 64 * 16;
   __shared__ __attribute__((aligned(16))) char smem[ROWS > PART ? ROWS : PART];
-  float* const hs = (float*)smem;          // [NB][16][P]
-  f32x4* const part = (f32x4*)smem;        // [wave][NB][NT][64], after the last columns
+  float* const hs = (float*)smem;          // [BUFS][NB][16][P]
+  f32x4* const part = (f32x4*)smem;        // [NB][chain or output tile][64], after the last columns
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = lane & 15, g = lane >> 4;
@@ -996,7 +995,7 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
     float s = 0.f, q = 0.f;
 #pragma unroll
     for (int j = 0; j < NI; ++j) s += (v[i][j].x + v[i][j].y) + (v[i][j].z + v[i][j].w);
-    mean[i] = wave_sum_dpp(s) / (float)D;
+    mean[i] = wave_sum(s) / (float)D;
 #pragma unroll
     for (int j = 0; j < NI; ++j)
       if (lane + 64 * j < nv) {
@@ -1004,7 +1003,7 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
                     d = v[i][j].w - mean[i];
         q += (a * a + b * b) + (c * c + d * d);
       }
-    rstd[i] = 1.0f / sqrtf(wave_sum_dpp(q) / (float)D + eps);
+    rstd[i] = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
   }
   // the modulation rows of the wave's two tokens
   const float* md[2];
@@ -1012,22 +1011,10 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
   for (int i = 0; i < 2; ++i)
     md[i] = mod + (size_t)rm.modrow[req_of_token(rm, min(tok0 + 2 * wave + i, T - 1))] * ld_mod;
 
-  // NA sums per output (16 outputs: four, a quarter of the terms each: shorter
-  // chains of additions, so less rounding, and four independent MFMA chains)
-  constexpr int NA = NT == 1 ? 4 : 1;
-  f32x4 acc[NB][NT][NA];
-#pragma unroll
-  for (int br = 0; br < NB; ++br)
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int a = 0; a < NA; ++a) acc[br][j][a] = f32x4{0.f, 0.f, 0.f, 0.f};
   constexpr int NCH = CH % 256 ? 1 : NI * 256 / CH;   // (whole rows when CH is no multiple of 256)
-#pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-    const int k0 = ch * CH;
-    if (k0 >= D) break;
-    if (ch > 0) __syncthreads();
+  // columns ch CH .. of the modulated rows into LDS
+  auto stage = [&](int ch) {
+    float* const to = hs + (BUFS > 1 ? ch % 2 : 0) * NB * 16 * P - ch * CH;
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
       // (with several chunks CH is a multiple of 256: a float4 column lies in one)
@@ -1046,60 +1033,143 @@ __global__ __launch_bounds__(512) void final_mfma_kernel(const float* __restrict
             y.y = (v[i][j].y - mean[i]) * rstd[i] * (1.f + b.y) + a.y;
             y.z = (v[i][j].z - mean[i]) * rstd[i] * (1.f + b.z) + a.z;
             y.w = (v[i][j].w - mean[i]) * rstd[i] * (1.f + b.w) + a.w;
-            *(float4*)&hs[(br * 16 + 2 * wave + t) * P + 4 * c - k0] = y;
+            *(float4*)&to[(br * 16 + 2 * wave + t) * P + 4 * c] = y;
           }
         }
       }
     }
-    __syncthreads();
-    const int kn = min(CH, D - k0);
-#pragma unroll 2
-    for (int k = 32 * wave + 8 * g; k < kn; k += 256) {
-      float w[NT][8];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) ld_w8(w_out + (size_t)(16 * j + fr) * D + k0 + k, w[j]);
-#pragma unroll
-      for (int br = 0; br < NB; ++br) {
-        float h[8];
-        ld_w8((const float*)&hs[(br * 16 + fr) * P + k], h);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-          for (int j = 0; j < NT; ++j)
-            acc[br][j][e % NA] =
-                __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][e], h[e], acc[br][j][e % NA], 0, 0, 0);
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int br = 0; br < NB; ++br)
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-      part[((wave * NB + br) * NT + j) * 64 + lane] =
-          NA == 4 ? (acc[br][j][0] + acc[br][j][1 % NA]) + (acc[br][j][2 % NA] + acc[br][j][3 % NA])
-                  : acc[br][j][0];
-  __syncthreads();
-  // lane: token fr, outputs 16 j + 4 g .. + 3
-  const int tok = tok0 + fr;
-  if (tok >= T) return;
-  const int r = req_of_token(rm, tok);
-  for (int j = wave; j < NT; j += 8) {
-    f32x4 y[2];
-    y[1] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int br = 0; br < NB; ++br) {
-      // the eight waves' sums, in pairs
-      f32x4 s[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) s[q] = part[((q * NB + br) * NT + j) * 64 + lane];
-      y[br] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
-    }
+  };
+  // a lane's eight weights: operand m of quad h is column 4 h + g of lane group m
+  typedef TW tw4 __attribute__((ext_vector_type(4)));
+  struct W8 {
+    tw4 q[2];
+  };
+  auto ld8 = [&](const TW* w) { return W8{{*(const tw4*)w, *(const tw4*)(w + 4)}}; };
+  // final sums of output tile j of both branches, in every lane: token fr,
+  // outputs 16 j + 4 g .. + 3
+  auto finish = [&](int j, f32x4 vc, f32x4 vu) {
+    const int tok = tok0 + fr;
+    if (tok >= T) return;
+    const int r = req_of_token(rm, tok);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int f = 16 * j + 4 * g + e;
       const float bo = to_f32(b_out[f]);
-      final_store(rm, tok, r, f, y[0][e] + bo, y[1][e] + bo, guidance, C, p, lat, noise_pred);
+      final_store(rm, tok, r, f, vc[e] + bo, vu[e] + bo, guidance, C, p, lat, noise_pred);
+    }
+  };
+
+  if constexpr (CHAINS) {
+    const int jt = blockIdx.y;   // output tile
+    const TW* const wp = w_out + (size_t)(16 * jt + fr) * D + 32 * wave + 8 * g;
+    f32x4 acc[NB][8];
+#pragma unroll
+    for (int br = 0; br < NB; ++br)
+#pragma unroll
+      for (int n = 0; n < 8; ++n) acc[br][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      const int k0 = ch * CH;
+      if (k0 >= D) break;
+      constexpr int NS = (CH + 255) / 256;   // 32-column steps of a wave
+      W8 wr[NS];
+      auto load_w = [&](int s) {
+        const int k = k0 + 256 * s;
+        if (k + 32 * wave < D) wr[s] = ld8(wp + k);
+      };
+      // (narrow rows: while they load; wide ones leave no registers for that)
+#pragma unroll
+      for (int s = 0; NCH == 1 && s < NS; ++s) load_w(s);
+      if (ch > 0) __syncthreads();
+      stage(ch);
+      __syncthreads();
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int k = 256 * s + 32 * wave;
+        if (k0 + k >= D) break;
+        if (NCH > 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_w(s);
+        }
+        float w[2][4];
+        transpose_groups(wr[s].q[0], w[0]);
+        transpose_groups(wr[s].q[1], w[1]);
+#pragma unroll
+        for (int br = 0; br < NB; ++br)
+#pragma unroll
+          for (int n = 0; n < 8; ++n)
+            acc[br][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                w[n & 1][n >> 1], hs[(br * 16 + fr) * P + k + 4 * n + g], acc[br][n], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int br = 0; br < NB; ++br)
+#pragma unroll
+      for (int n = 0; n < 8; ++n) part[(br * 64 + 8 * wave + n) * 64 + lane] = acc[br][n];
+    __syncthreads();
+    // the tree of wave_sum: chains 32, 16, 8 apart (wave n's share: chains 8 q + n) ...
+    auto pairs = [&](int c0, int step) {
+      f32x4 s[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s[q] = part[(c0 + step * q) * 64 + lane];
+      return ((s[0] + s[4]) + (s[2] + s[6])) + ((s[1] + s[5]) + (s[3] + s[7]));
+    };
+#pragma unroll
+    for (int br = 0; br < NB; ++br) part[(br * 64 + wave) * 64 + lane] = pairs(br * 64 + wave, 8);
+    __syncthreads();
+    // ... then 4, 2, 1
+    if (wave == 0) finish(jt, pairs(0, 1), NB == 2 ? pairs(64, 1) : f32x4{0.f, 0.f, 0.f, 0.f});
+  } else {
+    const int j = wave & 3, br = wave >> 2;
+    const bool works = br < NB;
+    const TW* const wp = w_out + (size_t)(16 * j + fr) * D + 8 * g;
+    const int steps = D / 32;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int PF = 4;   // weight loads in flight (CH / 32 is a multiple)
+    static_assert(CH % (32 * PF) == 0, "steps of a part");
+    W8 ring[PF];
+    if (works)
+#pragma unroll
+      for (int s = 0; s < PF; ++s) ring[s] = ld8(wp + 32 * min(s, steps - 1));
+    stage(0);
+    __syncthreads();
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      if (ch * CH >= D) break;
+      if (ch + 1 < NCH) stage(ch + 1);
+      if (works) {
+        // MFMA 2 m + c of a step takes columns 4 (2 m + c) + g, read one step ahead
+        const float* hp = hs + ((ch % 2 * NB + br) * 16 + fr) * P + g;
+        const int n = min(steps - ch * CH / 32, CH / 32);
+        float h[2][8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) h[0][q] = hp[4 * q];
+        for (int s0 = 0; s0 < n; s0 += PF) {
+#pragma unroll
+          for (int s = 0; s < PF; ++s) {
+            if (s0 + s >= n) break;
+            float w[2][4];
+            transpose_groups(ring[s].q[0], w[0]);
+            transpose_groups(ring[s].q[1], w[1]);
+            ring[s] = ld8(wp + 32 * min(ch * (CH / 32) + s0 + s + PF, steps - 1));
+            const float* hn = hp + 32 * min(s0 + s + 1, n - 1);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) h[(s + 1) & 1][q] = hn[4 * q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[q & 1][q >> 1], h[s & 1][q], acc, 0, 0, 0);
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if constexpr (NB == 1) {
+      if (works) finish(j, acc, acc);
+    } else {
+      if (br == 1) part[j * 64 + lane] = acc;
+      __syncthreads();
+      if (br == 0) finish(j, acc, part[j * 64 + lane]);
     }
   }
 }
@@ -1188,33 +1258,35 @@ hipError_t launch_final_layer(const float* x, const ReqMap& rm, const void* w_ou
                               float guidance, float* latents, float* noise_pred, hipStream_t st) {
   if (rm.tokens_total == 0) return hipSuccess;
   const int P = p * p * C, T = rm.tokens_total;
-#define T2I_FIN(K_, GRID_, BLOCK_, TW_)                                                          \
-  hipLaunchKernelGGL(K_, dim3(GRID_), dim3(BLOCK_), 0, st, x, rm, (const TW_*)w_out,             \
+#define T2I_FIN(K_, GX_, GY_, BLOCK_, TW_)                                                       \
+  hipLaunchKernelGGL(K_, dim3(GX_, GY_), dim3(BLOCK_), 0, st, x, rm, (const TW_*)w_out,          \
                      (const TW_*)b_out, mod, ld_mod, shift_off, scale_off, D, C, p, eps, guidance, \
                      latents, noise_pred)
   // (16-byte weight loads)
   const bool al = (uintptr_t)w_out % 16 == 0, two = rm.branches == 2;
   const int gt = (T + 15) / 16;
-#define T2I_FIN_NB(TW_, NT_, NI_, CH_)                                                           \
-  if (two) T2I_FIN((final_mfma_kernel<TW_, NT_, NI_, CH_, 2>), gt, 512, TW_);                    \
-  else T2I_FIN((final_mfma_kernel<TW_, NT_, NI_, CH_, 1>), gt, 512, TW_)
-  // rows of at most 1152 columns are staged whole, wider ones 1024 at a time
-#define T2I_FIN_MF(TW_)                                                                          \
-  if (P == 16 && D <= 1152 && al) {                                                              \
-    T2I_FIN_NB(TW_, 1, 5, 1152);                                                                 \
-  } else if (P == 16 && al) {                                                                    \
-    T2I_FIN_NB(TW_, 1, kMaxV4, 1024);                                                            \
-  } else if (P == 64 && al) {                                                                    \
-    T2I_FIN_NB(TW_, 4, kMaxV4, 1024);                                                            \
+#define T2I_FIN_NB(TW_, NI_, CH_, CHAINS_)                                                       \
+  if (two) T2I_FIN((final_mfma_kernel<TW_, NI_, CH_, 2, CHAINS_>), gt, (CHAINS_ ? P / 16 : 1), 512, TW_); \
+  else T2I_FIN((final_mfma_kernel<TW_, NI_, CH_, 1, CHAINS_>), gt, (CHAINS_ ? P / 16 : 1), 512, TW_)
+  // rows of at most 1152 columns are staged whole, wider ones in parts
+#define T2I_FIN_CHAINS(TW_)                                                                      \
+  if (D <= 1152) {                                                                               \
+    T2I_FIN_NB(TW_, 5, 1152, true);                                                              \
   } else {                                                                                       \
-    T2I_FIN((final_kernel<TW_>), (T + 3) / 4, 256, TW_);                                         \
+    T2I_FIN_NB(TW_, kMaxV4, 1024, true);                                                         \
   }
-  if (w_bf16) {
-    T2I_FIN_MF(bf16);
+  if (P == 64 && al && w_bf16) {
+    T2I_FIN_NB(bf16, kMaxV4, 512, false);
+  } else if (P == 16 && al && w_bf16) {
+    T2I_FIN_CHAINS(bf16);
+  } else if ((P == 16 || P == 64) && al && !w_bf16) {
+    T2I_FIN_CHAINS(float);
+  } else if (w_bf16) {
+    T2I_FIN((final_kernel<bf16>), (T + 3) / 4, 1, 256, bf16);
   } else {
-    T2I_FIN_MF(float);
+    T2I_FIN((final_kernel<float>), (T + 3) / 4, 1, 256, float);
   }
-#undef T2I_FIN_MF
+#undef T2I_FIN_CHAINS
 #undef T2I_FIN_NB
 #undef T2I_FIN
   return hipGetLastError();

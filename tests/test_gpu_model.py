@@ -597,3 +597,57 @@ def test_embedding_adds_in_feature_order(name, changes):
         x = x + np.concatenate([f(q[:, None] * om) for q in (i, j) for f in (np.sin, np.cos)],
                                1).astype(np.float32)
     assert np.array_equal(hid[:T].cpu().numpy(), x)
+
+
+FINAL_ORDER = [
+    ("tiny_f32", dict(latent_channels=4, requests=((2, 2),) * 19)),
+    ("tiny_f32", dict(latent_channels=16, requests=((2, 2),) * 5, guidance=3.0)),
+    ("tiny_f32", dict(latent_channels=3, requests=((2, 2),) * 5)),
+    ("tiny_f32", dict(latent_channels=4, requests=((2, 2),) * 5, hidden=1344, heads=21, guidance=3.0)),
+    ("mmdit1024", dict(latent_channels=4, requests=((8, 20),), hidden=1152, heads=9, guidance=3.0)),
+    ("mmdit1024", dict(requests=((8, 20),), hidden=1152, heads=9)),
+    ("mmdit1024", dict(requests=((8, 20),), hidden=256, heads=2, guidance=3.0)),
+]
+
+
+@pytest.mark.parametrize("name,changes", FINAL_ORDER)
+def test_final_layer_adds_in_one_order(name, changes):
+    """The final projection adds its columns as 64 chains (columns 4 l .. 4 l + 3
+    of every 256 in chain l) joined in the pairs of a wave's butterfly, or (64
+    outputs in bf16) in one ascending chain: bitwise, whichever kernel runs."""
+    w = synth.reduced(synth.workload(name), depth=1, steps=1, mlp_hidden=64, text_dim=64, **changes)
+    probe = t2i.weight_table(t2i.Config.from_shape(w))
+    host = synth.weights(w, probe)
+    at = {n: host[i] for i, (n, _) in enumerate(probe)}
+    # rows of +-1 (mean 0, variance 1; one-token requests, whose position
+    # embedding is 0 and 1), no scale: the modulated row is +-rstd + shift
+    D, P = w.hidden, w.patch_dim
+    sign = np.where(np.random.default_rng(3).permutation(D) < D // 2, 1.0, -1.0).astype(np.float32)
+    at["x_embed.w"][:] = 0
+    at["x_embed.b"][:] = sign if w.arch == "mmdit" else sign - np.arange(D) // (D // 4) % 2
+    at["final.ada.w"][:] = 0
+    at["final.ada.b"][D:] = 0
+    M = Model(w, weights=host)
+    v = step_gpu(M, M.latents_dev(synth.latents(w)), list(w.requests), [0.5] * w.n_req,
+                 M.text_dev(synth.texts(w)), guidance=w.guidance, n_blocks=0).astype(np.float32)
+    rstd = np.float32(1) / np.sqrt(np.float32(1) + np.float32(w.ln_eps))
+    h = (sign * rstd + at["final.ada.b"][:D]).astype(np.float32)
+    wo = at["final.out.w"].reshape(P, D)
+    if w.dtype == "bf16" and P == 64:
+        acc = np.zeros(P, np.float32)
+        for k in range(D):
+            acc = fma(wo[:, k], h[k], acc)
+    else:
+        acc = np.zeros((64, P), np.float32)
+        for k in range(D):
+            lane = k // 4 % 64
+            acc[lane] = fma(wo[:, k], h[k], acc[lane])
+        while len(acc) > 1:
+            acc = acc[:len(acc) // 2] + acc[len(acc) // 2:]
+        acc = acc[0]
+    ref = (acc + at["final.out.b"].ravel()).reshape(2, 2, w.latent_channels).transpose(2, 0, 1)
+    off = 0
+    for hh, ww in w.requests:
+        n = w.latent_channels * hh * ww
+        assert np.array_equal(v[off:off + n].reshape(-1, hh, ww), np.tile(ref, (1, hh // 2, ww // 2)))
+        off += n
