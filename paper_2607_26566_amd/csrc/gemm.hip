@@ -715,10 +715,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(
 // to MT activation rows (fp32, L2-resident), and reduce across the wave.
 // Weight reads are contiguous 1 KB per wave instruction.
 
-// NC columns per wave; all loads of a step (weights, then every row, rows past
-// the last repeated) are issued before its arithmetic, so that they cost one
-// latency and not one per row (1152 x 1152: 13.9 -> 7.1 us for 5 rows, 19.8 ->
-// 11.0 for 20, with one column per wave 6.4 -> 5.1 for one).
+// NC columns per wave.  With one column (the timestep MLP: few workgroups) all
+// loads of a step, weights and every row, rows past the last repeated, are
+// issued before its arithmetic, so that they cost one latency and not one per
+// row (1152 x 1152: 13.9 -> 7.1 us for 5 rows, 19.8 -> 11.0 for 20, with one
+// column per wave 6.4 -> 5.1 for one).  With four (the adaLN table, a workgroup
+// for every 16 of its columns) the chip is full and the waves per SIMD hide the
+// latency: rows are loaded where they are used, 86 registers and 5 waves for
+// 8 rows.  Loading them first took 142 and left 3 waves: the table of 28 blocks
+// of width 1152 took 729 instead of 513 us for 20 rows, 296 instead of 232 for
+// 8, 82 instead of 80 for one; 40 blocks of width 3072 5876 instead of 4416 for
+// 28; four rows at a time lie between (559 us for 20 rows).
 template <typename TW, int MT, int NC, int KIND>
 __device__ __forceinline__ void linear_rows_body(const float* __restrict__ A, int lda,
                                                  const TW* __restrict__ W, int ldw,
@@ -737,7 +744,6 @@ __device__ __forceinline__ void linear_rows_body(const float* __restrict__ A, in
 #pragma unroll(NC == 1 && MT <= 2 ? 4 : 1)
   for (int k = lane * 8; k < K; k += 64 * 8) {
     float wv[NC][8];
-    float4 a[MT], b[MT];
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
       const int n = min(n0 + j, N - 1);
@@ -752,21 +758,31 @@ __device__ __forceinline__ void linear_rows_body(const float* __restrict__ A, in
         wv[j][4] = b.x; wv[j][5] = b.y; wv[j][6] = b.z; wv[j][7] = b.w;
       }
     }
+    auto add_row = [&](int m, float4 a, float4 b) {
+      const float av[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      const float* ap = A + (size_t)(m0 + min(m, mt - 1)) * lda + k;
-      a[m] = *(const float4*)ap;
-      b[m] = *(const float4*)(ap + 4);
-    }
+      for (int j = 0; j < NC; ++j)
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      if (m < mt) {
-        const float av[8] = {a[m].x, a[m].y, a[m].z, a[m].w, b[m].x, b[m].y, b[m].z, b[m].w};
+        for (int e = 0; e < 8; ++e) acc[m][j] = fmaf(av[e], wv[j][e], acc[m][j]);
+    };
+    if constexpr (NC == 1) {
+      float4 a[MT], b[MT];
 #pragma unroll
-        for (int j = 0; j < NC; ++j)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[m][j] = fmaf(av[e], wv[j][e], acc[m][j]);
+      for (int m = 0; m < MT; ++m) {
+        const float* ap = A + (size_t)(m0 + min(m, mt - 1)) * lda + k;
+        a[m] = *(const float4*)ap;
+        b[m] = *(const float4*)(ap + 4);
       }
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        if (m < mt) add_row(m, a[m], b[m]);
+    } else {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        if (m < mt) {
+          const float* ap = A + (size_t)(m0 + m) * lda + k;
+          add_row(m, *(const float4*)ap, *(const float4*)(ap + 4));
+        }
     }
   }
 #pragma unroll
