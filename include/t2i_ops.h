@@ -31,7 +31,9 @@ typedef enum {
  * Linear layer (DiT projections, Sec. 4's model `forward`): y = A W^T + b,
  * A [M, K] with row stride lda, W [N, K] with row stride ldw, b [N].
  *   dtype T2I_BF16: A, W, b bf16, MFMA with fp32 accumulation, K % 64 == 0,
- *                   lda, ldw % 8 == 0.  `out` is bf16.
+ *                   lda, ldw % 8 == 0.  `out` is bf16.  A and W that start
+ *                   at a multiple of 16 bytes are loaded straight into LDS,
+ *                   others through registers: same results, more time.
  *   dtype T2I_F32 : A, W, b, out fp32.
  * For T2I_EPI_RESID*: `resid` is fp32 [M, N] (stride ldr) updated in place,
  * `resid_copy` (bf16 [M, N], stride ldr, or NULL) receives its new value;

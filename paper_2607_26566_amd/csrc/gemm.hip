@@ -449,10 +449,11 @@ hipError_t launch_gemm_bf16(const bf16* A, int lda, const bf16* W, int ldw, cons
   // Direct HBM->LDS loads (gemm_dma.hip) for widths of whole tiles, with K
   // split over several workgroups where the caller allows it and a layer of
   // few rows against a long K would leave CUs idle (e.g. the 512-row text
-  // stream against K = 3072 or 12288); register-staged tiles for other widths
-  // and for operands past the direct loads' 32-bit byte offsets.
+  // stream against K = 3072 or 12288); register-staged tiles for other widths,
+  // for operands past the direct loads' 32-bit byte offsets and for operands
+  // that are not 16-byte aligned (a lane's direct load moves 16 bytes).
   const bool dma = (size_t)2 * M * lda < 0x7fffffff && (size_t)2 * N * ldw < 0x7fffffff &&
-                   gemm_dma_fits(M, N);
+                   al(A, 16) && al(W, 16) && gemm_dma_fits(M, N);
   // (from 2048 rows on there are tiles enough without splitting K)
   int splits = splitk_ws && kind != EPI_SILU && !(dma && M >= 2048) ? splitk_factor(N, K) : 1;
   if ((size_t)splits * M * N > splitk_floats) splits = 1;

@@ -27,12 +27,25 @@ def rnd(seed, shape, std=1.0, bf=True):
     return synth.round_bf16(a) if bf else a
 
 
-def run_linear(dtype, epi, A, W, b, resid=None, gate=None, with_copy=False):
+def off_16_bytes(t):
+    """A copy of a bf16 matrix that starts 8 bytes past a 16-byte boundary."""
+    buf = torch.empty(t.numel() + 4, dtype=t.dtype, device=t.device)
+    buf[4:] = t.ravel()
+    out = buf[4:].view(t.shape)
+    assert out.data_ptr() % 16 == 8
+    return out
+
+
+def run_linear(dtype, epi, A, W, b, resid=None, gate=None, with_copy=False, off_a=False, off_w=False):
     lib = t2i.load()
     M, K = A.shape
     N = W.shape[0]
     dt = "bf16" if dtype == _lib.T2I_BF16 else "f32"
     dA, dW, db = to_dev(A, dt), to_dev(W, dt), to_dev(b, dt)
+    if off_a:
+        dA = off_16_bytes(dA)
+    if off_w:
+        dW = off_16_bytes(dW)
     out = torch.zeros((M, N), dtype=dA.dtype, device=DEV)
     dR = torch.from_numpy(resid.astype(np.float32)).to(DEV) if resid is not None else None
     dC = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV) if with_copy else None
@@ -184,6 +197,24 @@ def test_linear_bf16_every_tile(M, N, tile, K):
     _, few, _ = run_linear(_lib.T2I_BF16, _lib.T2I_EPI_RESID_GATED, A[tail], W, b, resid=x0[tail],
                            gate=gate)
     assert torch.equal(few, x[tail])
+
+
+# few rows, widths of 128 below and at 2048 rows, of 144, an activation and the
+# gated update
+@pytest.mark.parametrize("M,N,K,epi", [(33, 1152, 640, 0), (300, 2048, 128, 2), (2100, 4096, 192, 1),
+                                       (130, 3456, 64, 4)])
+def test_linear_bf16_operands_off_16_bytes(M, N, K, epi):
+    """A and W that start 8 bytes past a 16-byte boundary (the second half of a
+    row's first 16 bytes): the bits of the aligned call, which the direct loads
+    compute."""
+    say(f"linear bf16 off 16 bytes {M}x{N}x{K} epi {epi}")
+    A, W, b = rnd(100, (M, K)), rnd(101, (N, K), 0.05), rnd(102, (N,), 0.1)
+    x0 = rnd(103, (M, N), bf=False) if epi >= 3 else None
+    gate = rnd(104, (N,), 0.5, bf=False) if epi == 4 else None
+    out, x, _ = run_linear(_lib.T2I_BF16, epi, A, W, b, resid=x0, gate=gate)
+    for off in (dict(off_a=True), dict(off_w=True), dict(off_a=True, off_w=True)):
+        got, xg, _ = run_linear(_lib.T2I_BF16, epi, A, W, b, resid=x0, gate=gate, **off)
+        assert torch.equal(got, out) and (xg is None or torch.equal(xg, x))
 
 
 @pytest.mark.parametrize("M,N,K,epi", [(64, 128, 256, 0), (100, 520, 128, 2), (77, 33, 90, 4)])
