@@ -212,6 +212,13 @@ Layout layout(const t2i_dit_config& c) {
 
 // ---------------------------------------------------------------------------
 
+// Lets this thread allocate and free while a stream is being captured.
+struct CaptureRelaxed {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 struct t2i_dit {
   t2i_dit_config cfg;
   std::vector<const void*> w;
@@ -220,7 +227,7 @@ struct t2i_dit {
   Layout L{};
   std::string err;
   // page-locked copy of the cache headers that the decision kernel writes
-  // itself (created by the first cache check)
+  // itself; NULL where t2i_dit_init could get none
   CacheHeader* hdr_host = nullptr;
   // kernel timing
   uint32_t prof_mask = 0;
@@ -244,7 +251,10 @@ struct t2i_dit {
         (void)hipEventDestroy(blk_ev[b]);
       }
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
-    if (hdr_host) (void)hipHostFree(hdr_host);
+    if (hdr_host) {
+      CaptureRelaxed r;
+      (void)hipHostFree(hdr_host);
+    }
   }
 
   template <typename T>
@@ -872,19 +882,22 @@ t2i_status cache_check_impl(t2i_dit* h, const Plan& P, int step, int n_steps, do
   double* partial = h->at<double>(h->L.partial);
   // block 0's first LN-modulation (MMDiT: of the image stream)
   const int sh = is_mmdit(h) ? 6 * c.hidden : 0;
-  if (!h->hdr_host)
-    HIP_TRY(h, hipHostMalloc((void**)&h->hdr_host, sizeof(CacheHeader) * kMaxReq,
-                             hipHostMallocDefault));
   HIP_TRY(h, prof_mark(h, T2I_K_CACHE, true, st));
   HIP_TRY(h, launch_cache_signal(h->at<float>(h->L.x0), P.rm, h->at<float>(h->L.mod),
                                  mod_width(c), sh, sh + c.hidden, c.hidden, c.ln_eps, cp.m_prev,
                                  cp.hdr, step, partial, st));
   HIP_TRY(h, launch_cache_decide(P.rm, partial, cp.hdr, h->hdr_host, step, n_steps, tau, mode, st));
   HIP_TRY(h, prof_mark(h, T2I_K_CACHE, false, st));
+  CacheHeader copy[kMaxReq];
+  const CacheHeader* hdr = h->hdr_host;
+  if (!hdr) {
+    HIP_TRY(h, hipMemcpyAsync(copy, cp.hdr, sizeof(CacheHeader) * P.n_req, hipMemcpyDeviceToHost, st));
+    hdr = copy;
+  }
   HIP_TRY(h, hipStreamSynchronize(st));
   for (int r = 0; r < P.n_req; ++r) {
-    if (rel_l1) rel_l1[r] = h->hdr_host[r].d;
-    if (skip) skip[r] = (uint8_t)(h->hdr_host[r].skip ? 1 : 0);
+    if (rel_l1) rel_l1[r] = hdr[r].d;
+    if (skip) skip[r] = (uint8_t)(hdr[r].skip ? 1 : 0);
   }
   return T2I_OK;
 }
@@ -1141,6 +1154,15 @@ t2i_status t2i_dit_init(const t2i_dit_config* cfg, const void* const* weights, v
   h->ws_bytes = ws_bytes;
   h->L = layout(*cfg);
   h->blk.assign(cfg->depth, t2i_dit::BLK_RESIDENT);
+  {
+    // here, so that no later call allocates; any device may be current then
+    CaptureRelaxed r;
+    if (hipHostMalloc((void**)&h->hdr_host, sizeof(CacheHeader) * kMaxReq, hipHostMallocPortable) !=
+        hipSuccess) {
+      h->hdr_host = nullptr;   // (no GPU, for one) cache checks copy the headers back
+      (void)hipGetLastError();
+    }
+  }
   *out = h;
   return T2I_OK;
 }

@@ -1302,7 +1302,7 @@ hipError_t launch_final_layer(const float* x, const ReqMap& rm, const void* w_ou
 // (lane order, butterfly, then waves 0..15); m_prev := m.
 // cache_decide_kernel: one wave per request sums its partials (lane l the
 // blocks l, l + 64, .. in order, then a butterfly), applies the rule and also
-// writes the header to page-locked host memory for the caller.
+// writes the header to page-locked host memory for the caller, if given.
 
 int cache_partial_blocks(const ReqMap& rm) {
   int n = 0;
@@ -1437,7 +1437,7 @@ __global__ void cache_decide_kernel(ReqMap rm, const double* __restrict__ partia
   hd.skip = skip;
   hd.has_m = 1;
   hdr[r] = hd;
-  host[r] = hd;
+  if (host) host[r] = hd;
 }
 
 hipError_t launch_cache_signal(const float* x0, const ReqMap& rm, const float* mod, int ld_mod,

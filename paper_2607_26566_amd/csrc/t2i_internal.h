@@ -333,7 +333,7 @@ int cache_partial_blocks(const ReqMap& rm);
 hipError_t launch_cache_signal(const float* x0, const ReqMap& rm, const float* mod, int ld_mod,
                                int shift_off, int scale_off, int D, float eps, float* m_prev,
                                CacheHeader* hdr, int step, double* partial, hipStream_t st);
-// host: page-locked copy of the headers (device-visible)
+// host: page-locked copy of the headers (device-visible), or NULL
 hipError_t launch_cache_decide(const ReqMap& rm, const double* partial, CacheHeader* hdr,
                                CacheHeader* host, int step, int n_steps, double tau, int mode,
                                hipStream_t st);

@@ -36,6 +36,22 @@ def test_library_exports_every_declared_symbol():
         assert name in _lib.SIGNATURES, name
 
 
+def test_only_handle_creation_allocates():
+    """Steps, samples and cache checks may run where nothing may be allocated:
+    the sources name an allocation inside t2i_dit_init alone."""
+    src = os.path.join(ROOT, "paper_2607_26566_amd", "csrc")
+    found = []
+    for f in sorted(os.listdir(src)):
+        func = None
+        for line in open(os.path.join(src, f)):
+            m = re.match(r"[\w:<>*& ]*?\b(\w+)\(", line)   # definitions start in column 0
+            if m and line[0].isalpha():
+                func = m[1]
+            if re.search(r"\bhip\w*Malloc\w*\s*\(", line.split("//")[0]):
+                found.append((f, func))
+    assert found == [("api.cpp", "t2i_dit_init")]
+
+
 def test_struct_sizes_match_header_layout():
     # field order and types mirror include/t2i_dit.h; sizes are what the
     # library checks through struct_size
