@@ -338,8 +338,11 @@ __global__ __launch_bounds__(256) void embed_mfma_kernel(const float* __restrict
   __shared__ __attribute__((aligned(16))) EmbedTokens<16, P + 4> es;
   const int lane = threadIdx.x & 63, fr = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int T = rm.tokens_total, t0 = blockIdx.y * 16;
-  const int qd = D / 4, d00 = (blockIdx.x * 4 + wave) * ET * 16;
+  // the workgroups of a token tile are neighbours, all in grid x (grid y ends at
+  // 65535 workgroups, a million tokens)
+  const int gy = (D + 64 * ET - 1) / (64 * ET), tile = blockIdx.x / gy;
+  const int T = rm.tokens_total, t0 = tile * 16;
+  const int qd = D / 4, d00 = (((int)blockIdx.x - tile * gy) * 4 + wave) * ET * 16;
   // the wave's weights and biases, fetched while the patches are gathered
   // (channel tiles past D repeat the last one and are not stored)
   typedef TW tw4 __attribute__((ext_vector_type(4)));
@@ -458,12 +461,12 @@ hipError_t launch_embed(const float* lat, const ReqMap& rm, const void* w_pe, co
                      (const TW_*)b_pe, D, C, p, pe_table, x0, x, copies)
   // 6 channel tiles per wave (1152 channels: 3 workgroups per 16 tokens)
   constexpr int ET = 6;
-  const int gx = (T + 15) / 16, gy = (D + 64 * ET - 1) / (64 * ET);
+  const int gx = (T + 15) / 16 * ((D + 64 * ET - 1) / (64 * ET));
   // (aligned weight rows, 16-byte vectors of the outputs)
   const bool mf = (uintptr_t)w_pe % 16 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)x0 % 16 == 0;
 #define T2I_EMB_ANY(TW_)                                                                       \
-  if (P == 16 && mf) T2I_EMB((embed_mfma_kernel<TW_, 1, ET>), TW_, gy, gx);                    \
-  else if (P == 64 && mf) T2I_EMB((embed_mfma_kernel<TW_, 4, ET>), TW_, gy, gx);               \
+  if (P == 16 && mf) T2I_EMB((embed_mfma_kernel<TW_, 1, ET>), TW_, gx, 1);                     \
+  else if (P == 64 && mf) T2I_EMB((embed_mfma_kernel<TW_, 4, ET>), TW_, gx, 1);                \
   else T2I_EMB((embed_kernel<TW_>), TW_, (T + kEmbTok - 1) / kEmbTok, (D + 255) / 256)
   if (w_bf16) {
     T2I_EMB_ANY(bf16);

@@ -651,3 +651,33 @@ def test_final_layer_adds_in_one_order(name, changes):
         n = w.latent_channels * hh * ww
         assert np.array_equal(v[off:off + n].reshape(-1, hh, ww), np.tile(ref, (1, hh // 2, ww // 2)))
         off += n
+
+
+@pytest.mark.parametrize("channels", [4, 3])
+def test_embedding_past_a_million_tokens(channels):
+    """More 16-token tiles than one grid dimension but the first holds: the
+    first and the last request of such a batch are bitwise what they are alone
+    (fp32, which bounds the tokens of a call by memory alone)."""
+    side, n = 512, 17                         # 17 x 65536 = 1 114 112 tokens
+    w = synth.reduced(synth.workload("tiny_f32"), depth=1, steps=1, guidance=1.0, hidden=64, heads=1,
+                      mlp_hidden=64, text_dim=64, latent_channels=channels,
+                      requests=((side, side),) * n)
+    T, per = side * side // 4, channels * side * side
+    assert n * T > 65535 * 16
+    M = Model(w)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    lat = torch.randn(n * per, generator=g, device=DEV)
+    text = torch.zeros((n, w.text_tokens, w.text_dim), device=DEV)
+
+    def embedding(first, count):
+        hid = torch.zeros((count * T, w.hidden), device=DEV)
+        step_gpu(M, lat[first * per:(first + count) * per].clone(), [(side, side)] * count,
+                 [0.5] * count, text[:count].contiguous(), n_blocks=0, hidden_out=hid)
+        return hid
+
+    whole = embedding(0, n)
+    for r in (0, n - 1):
+        assert torch.equal(whole[r * T:(r + 1) * T], embedding(r, 1))
+    assert whole[-T:].any()
+    del whole, lat, M
+    torch.cuda.empty_cache()
