@@ -1314,9 +1314,10 @@ int cache_partial_blocks(const ReqMap& rm) {
   return n;
 }
 
-// NI: float4 per lane (D <= 256 NI)
-template <int NI>
-__global__ __launch_bounds__(64 * kCacheRowsPerBlock) void cache_signal_kernel(
+// NI: float4 per lane (D <= 256 NI); NW: waves, each with 16 / NW rows in turn
+// (16 waves leave a lane 128 registers: too few for two rows of 3072 columns)
+template <int NI, int NW>
+__global__ __launch_bounds__(64 * NW) void cache_signal_kernel(
     const float* __restrict__ x0, ReqMap rm, const float* __restrict__ mod, int ld_mod,
     int shift_off, int scale_off, int D, float eps, float* __restrict__ m_prev,
     const CacheHeader* __restrict__ hdr, int step, double* __restrict__ partial) {
@@ -1332,62 +1333,65 @@ __global__ __launch_bounds__(64 * kCacheRowsPerBlock) void cache_signal_kernel(
     ++r;
   }
   const int nv = D >> 2;
-  const int tok = rm.tok_off[r] + ((int)blockIdx.x - base) * kCacheRowsPerBlock + wave;
-  double num = 0.0, den = 0.0;
-  if (tok < rm.tok_off[r + 1]) {
-    const bool have_prev = step > 0 && hdr[r].has_m;
-    const float* md = mod + (size_t)rm.modrow[r] * ld_mod;
-    const float4* sh = (const float4*)(md + shift_off);
-    const float4* sc = (const float4*)(md + scale_off);
-    const float4* xr = (const float4*)(x0 + (size_t)tok * D);
-    float4* mr = (float4*)(m_prev + (size_t)tok * D);
-    float4 v[NI], o[NI];
-    float s = 0.f;
+#pragma unroll 1
+  for (int row = wave; row < kCacheRowsPerBlock; row += NW) {
+    double num = 0.0, den = 0.0;
+    const int tok = rm.tok_off[r] + ((int)blockIdx.x - base) * kCacheRowsPerBlock + row;
+    if (tok < rm.tok_off[r + 1]) {
+      const bool have_prev = step > 0 && hdr[r].has_m;
+      const float* md = mod + (size_t)rm.modrow[r] * ld_mod;
+      const float4* sh = (const float4*)(md + shift_off);
+      const float4* sc = (const float4*)(md + scale_off);
+      const float4* xr = (const float4*)(x0 + (size_t)tok * D);
+      float4* mr = (float4*)(m_prev + (size_t)tok * D);
+      float4 v[NI], o[NI];
+      float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int c = lane + 64 * i;
-      v[i] = o[i] = float4{0.f, 0.f, 0.f, 0.f};
-      if (c < nv) v[i] = xr[c];
-      if (c < nv && have_prev) o[i] = mr[c];
-    }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-    const float mean = wave_sum(s) / (float)D;
-    float q = 0.f;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nv) {
-        const float a = v[i].x - mean, b = v[i].y - mean, cc = v[i].z - mean, d = v[i].w - mean;
-        q += (a * a + b * b) + (cc * cc + d * d);
+      for (int i = 0; i < NI; ++i) {
+        const int c = lane + 64 * i;
+        v[i] = o[i] = float4{0.f, 0.f, 0.f, 0.f};
+        if (c < nv) v[i] = xr[c];
+        if (c < nv && have_prev) o[i] = mr[c];
       }
-    }
-    const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nv) {
-        const float4 a = sh[c], b = sc[c];
-        float4 m;
-        m.x = (v[i].x - mean) * rstd * (1.f + b.x) + a.x;
-        m.y = (v[i].y - mean) * rstd * (1.f + b.y) + a.y;
-        m.z = (v[i].z - mean) * rstd * (1.f + b.z) + a.z;
-        m.w = (v[i].w - mean) * rstd * (1.f + b.w) + a.w;
-        if (have_prev) {
-          num += (double)fabsf(m.x - o[i].x) + (double)fabsf(m.y - o[i].y) +
-                 (double)fabsf(m.z - o[i].z) + (double)fabsf(m.w - o[i].w);
-          den += (double)fabsf(o[i].x) + (double)fabsf(o[i].y) + (double)fabsf(o[i].z) +
-                 (double)fabsf(o[i].w);
+      for (int i = 0; i < NI; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+      const float mean = wave_sum(s) / (float)D;
+      float q = 0.f;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int c = lane + 64 * i;
+        if (c < nv) {
+          const float a = v[i].x - mean, b = v[i].y - mean, cc = v[i].z - mean, d = v[i].w - mean;
+          q += (a * a + b * b) + (cc * cc + d * d);
         }
-        mr[c] = m;
+      }
+      const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int c = lane + 64 * i;
+        if (c < nv) {
+          const float4 a = sh[c], b = sc[c];
+          float4 m;
+          m.x = (v[i].x - mean) * rstd * (1.f + b.x) + a.x;
+          m.y = (v[i].y - mean) * rstd * (1.f + b.y) + a.y;
+          m.z = (v[i].z - mean) * rstd * (1.f + b.z) + a.z;
+          m.w = (v[i].w - mean) * rstd * (1.f + b.w) + a.w;
+          if (have_prev) {
+            num += (double)fabsf(m.x - o[i].x) + (double)fabsf(m.y - o[i].y) +
+                   (double)fabsf(m.z - o[i].z) + (double)fabsf(m.w - o[i].w);
+            den += (double)fabsf(o[i].x) + (double)fabsf(o[i].y) + (double)fabsf(o[i].z) +
+                   (double)fabsf(o[i].w);
+          }
+          mr[c] = m;
+        }
       }
     }
-  }
-  num = wave_sum(num);
-  den = wave_sum(den);
-  if (lane == 0) {
-    red[wave][0] = num;
-    red[wave][1] = den;
+    num = wave_sum(num);
+    den = wave_sum(den);
+    if (lane == 0) {
+      red[row][0] = num;
+      red[row][1] = den;
+    }
   }
   __syncthreads();
   if (threadIdx.x < 2) {
@@ -1448,11 +1452,11 @@ hipError_t launch_cache_signal(const float* x0, const ReqMap& rm, const float* m
                                CacheHeader* hdr, int step, double* partial, hipStream_t st) {
   const int nb = cache_partial_blocks(rm);
   if (nb == 0) return hipSuccess;
-#define T2I_SIG(NI_)                                                                           \
-  hipLaunchKernelGGL((cache_signal_kernel<NI_>), dim3(nb), dim3(64 * kCacheRowsPerBlock), 0, st, x0, \
-                     rm, mod, ld_mod, shift_off, scale_off, D, eps, m_prev, hdr, step, partial)
-  if (D <= 1280) T2I_SIG(5);
-  else T2I_SIG(kMaxV4);
+#define T2I_SIG(NI_, NW_)                                                                     \
+  hipLaunchKernelGGL((cache_signal_kernel<NI_, NW_>), dim3(nb), dim3(64 * NW_), 0, st, x0, rm, mod, \
+                     ld_mod, shift_off, scale_off, D, eps, m_prev, hdr, step, partial)
+  if (D <= 1280) T2I_SIG(5, 16);
+  else T2I_SIG(kMaxV4, 8);
 #undef T2I_SIG
   return hipGetLastError();
 }

@@ -34,7 +34,8 @@ def kernels(tmp_path_factory):
                     sym = re.search(r"\.symbol:\s+(\S+)\.kd", block)
                     if sym:
                         out[sym[1]] = {k: int(re.search(rf"\.{k}:\s+(\d+)", block)[1])
-                                       for k in ("vgpr_count", "vgpr_spill_count")}
+                                       for k in ("vgpr_count", "vgpr_spill_count",
+                                                 "private_segment_fixed_size")}
             entry += 24 + n
     assert os.path.getsize(fat) and out
     return out
@@ -52,3 +53,8 @@ def test_conditioning_rows_keep_five_waves_per_simd(kernels):
     for k, v in {**find(kernels, "linear_rows_group_kernel"), **find(kernels, "linear_rows_kernel")}.items():
         assert (v["vgpr_count"] + 7) // 8 * 8 * 5 <= 512, (k, v)
         assert v["vgpr_spill_count"] == 0, (k, v)
+
+
+def test_cache_signal_does_not_spill(kernels):
+    for k, v in find(kernels, "cache_signal_kernel").items():
+        assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (k, v)
