@@ -997,7 +997,9 @@ hipError_t gemm_dma_dispatch(const bf16* A, int lda, const bf16* W, int ldw, con
 // columns, and the cost of one round of 256 workgroups in hundredths of a
 // microsecond per K step of 64, from K = 2048 on (measured on MI355X at K =
 // 3072 .. 12288, rounds from half full on) and below (K = 1152, scaled alike:
-// there the prologue and epilogue weigh differently).
+// there the prologue and epilogue weigh differently; a round of 256 x 128 costs
+// there what two of 128 x 128 do, which never number more, and as the earlier
+// shape it is taken: 8192 x 1024 x 1024 gated 29 us against 40).
 //
 // One workgroup per CU (the rings take most of the LDS), so a launch costs its
 // rounds times the tile's cost; the cheapest shape that divides N is taken.
@@ -1027,7 +1029,7 @@ struct DmaTile {
 };
 constexpr DmaTile kDmaTiles[] = {
     {256, 288, 176, 195}, {256, 256, 165, 205}, {256, 192, 128, 133}, {256, 144, 113, 105},
-    {256, 128, 95, 108},  {128, 192, 78, 78},   {128, 144, 68, 68},   {128, 128, 53, 53},
+    {256, 128, 95, 106},  {128, 192, 78, 78},   {128, 144, 68, 68},   {128, 128, 53, 53},
     {64, 144, 45, 45},    {64, 128, 42, 42},    {32, 144, 37, 37},    {32, 128, 35, 35},
     {32, 64, 25, 25},
 };
@@ -1038,13 +1040,11 @@ bool gemm_dma_fits(int M, int N) {
   return N % 144 == 0 || N % 128 == 0 || (N % 64 == 0 && M <= 64);
 }
 
-// splits > 1: EPI_PARTIAL, K per slice (grid row).
-hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
-                           int M, int N, int K, int kind, const Epi& epi, int vec_ok,
-                           hipStream_t st, int splits) {
+// the cheapest tile shape, and how many of them the launch has
+static DmaTile dma_tile(int M, int N, int K, int kind, int splits, long& tiles) {
   const bool longk = K >= 2048;
   DmaTile t{0, 0, 0, 0};
-  long best = -1, tiles = 0;
+  long best = -1;
   for (const DmaTile& c : kDmaTiles) {
     if (N % c.bn || (kind == EPI_PARTIAL && c.bm == 256)) continue;
     const long n = (long)((M + c.bm - 1) / c.bm) * (N / c.bn) * splits;
@@ -1055,6 +1055,16 @@ hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const
       tiles = n;
     }
   }
+  return t;
+}
+
+// splits > 1: EPI_PARTIAL, K per slice (grid row).
+hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const bf16* bias,
+                           int M, int N, int K, int kind, const Epi& epi, int vec_ok,
+                           hipStream_t st, int splits) {
+  const bool longk = K >= 2048;
+  long tiles = 0;
+  const DmaTile t = dma_tile(M, N, K, kind, splits, tiles);
   // row blocks per tile group (see gemm_dma_kernel): 8 for long K, 2 for the
   // 288-wide tiles at short K, 1 for the 144-wide residual updates
   const bool resid = kind == EPI_RESID || kind == EPI_RESID_GATED;
@@ -1084,6 +1094,15 @@ hipError_t launch_gemm_dma(const bf16* A, int lda, const bf16* W, int ldw, const
   T2I_TILE(32, 64, 2, 4, 7, 16)
 #undef T2I_TILE
   return hipErrorInvalidValue;
+}
+
+extern "C" int t2i_test_dma_tile(int M, int N, int K, int kind, int* rows, int* columns) {
+  if (M < 1 || N < 1 || K < 1 || !gemm_dma_fits(M, N)) return 0;
+  long tiles = 0;
+  const DmaTile t = dma_tile(M, N, K, kind, 1, tiles);
+  *rows = t.bm;
+  *columns = t.bn;
+  return 1;
 }
 
 // The cross-attention query projection with the cross-attention fused in

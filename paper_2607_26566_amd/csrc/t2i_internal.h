@@ -205,6 +205,11 @@ hipError_t launch_gemm_bf16(const bf16* A, int lda, const bf16* W, int ldw, cons
 hipError_t launch_gemm_f32(const float* A, int lda, const float* W, int ldw, const float* bias,
                            int M, int N, int K, int kind, const Epi& epi, hipStream_t st);
 
+// For the tests, which assert that a shape reaches the path it is there for
+// (host arithmetic only): the direct-load tile of a bf16 layer (0: it takes
+// register-staged tiles).
+extern "C" int t2i_test_dma_tile(int M, int N, int K, int kind, int* rows, int* columns);
+
 // Conditioning GEMMs: A fp32 [M, K], W fp32 or bf16 [N, K]; STORE or SILU.
 // Per-group operand table of a grouped launch (by value in the kernel
 // arguments): group i uses W[i], bias[i] and writes out[i] (vt[i]).

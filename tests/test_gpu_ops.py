@@ -27,6 +27,12 @@ def rnd(seed, shape, std=1.0, bf=True):
     return synth.round_bf16(a) if bf else a
 
 
+def dma_tile(M, N, K, epi=0):
+    """(rows, columns) of the direct-load tile a bf16 layer takes, None: register-staged."""
+    r, c = C.c_int(), C.c_int()
+    return (r.value, c.value) if t2i.load().t2i_test_dma_tile(M, N, K, epi, C.byref(r), C.byref(c)) else None
+
+
 def off_16_bytes(t):
     """A copy of a bf16 matrix that starts 8 bytes past a 16-byte boundary."""
     buf = torch.empty(t.numel() + 4, dtype=t.dtype, device=t.device)
@@ -76,20 +82,22 @@ def test_linear_bf16_store_and_gelu(M, N, K):
     assert rel_l2(to_host(out), dit.gelu_tanh(ref)) < 3e-3
 
 
-def test_linear_bf16_tilings_agree_bitwise():
-    """The same rows through the three GEMM kernels -- direct-load 256-row
-    tiles (2100 rows), register-staged 128 x 144 tiles (1900 rows) and 64 x 64
-    tiles (300 rows) -- come out bitwise equal: every kernel accumulates K in
-    the same order, which is what makes a packed batch equal its requests run
-    alone."""
-    N, K = 4608, 1152
+@pytest.mark.parametrize("N", [4608, 2048])   # widths of 144 and of 128
+def test_linear_bf16_tilings_agree_bitwise(N):
+    """The same rows through direct-load tiles of three heights and, from A off
+    its 16-byte boundary, through the register-staged tiles (128 x 144 at 1900
+    rows of width 4608, else 64 x 64) come out bitwise equal: every kernel accumulates K
+    in the same order, which is what makes a packed batch equal its requests
+    run alone."""
+    K = 1152
     A, W, b = rnd(70, (2100, K)), rnd(71, (N, K), 0.05), rnd(72, (N,), 0.1)
-    outs = []
-    for M in (2100, 1900, 300):
-        out, _, _ = run_linear(_lib.T2I_BF16, _lib.T2I_EPI_GELU, A[:M], W, b)
-        outs.append(to_host(out)[:300])
-    say(f"tilings: max |diff| {np.abs(outs[0] - outs[1]).max():.1e}, {np.abs(outs[0] - outs[2]).max():.1e}")
-    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+    first, _, _ = run_linear(_lib.T2I_BF16, _lib.T2I_EPI_GELU, A, W, b)
+    heights = {dma_tile(2100, N, K)[0]}
+    for M, off in ((1900, False), (300, False), (40, False), (1900, True), (300, True)):
+        out, _, _ = run_linear(_lib.T2I_BF16, _lib.T2I_EPI_GELU, A[:M], W, b, off_a=off)
+        assert torch.equal(out, first[:M])
+        heights |= {dma_tile(M, N, K)[0]}
+    assert len(heights) >= 3
 
 
 @pytest.mark.parametrize("M,N,K", [(300, 192, 128), (1000, 1152, 4608), (8192, 1152, 1152),
@@ -163,21 +171,24 @@ def test_linear_bf16_operand_over_2gib():
 
 
 # one shape per tile of the direct-load GEMM (rows x columns of the tile it
-# takes), rows not a multiple of the tile's
+# takes), rows not a multiple of the tile's, with the contractions: one K step
+# of 64, an odd number of steps, and more steps than any ring has stages (7), so
+# that every stage is refilled
 DMA_TILE_SHAPES = [(17, 1152, "32x64"), (33, 9216, "32x128"), (100, 9216, "32x144"),
                    (65, 12288, "64x128"), (900, 2304, "64x144"), (130, 12288, "128x128"),
-                   (900, 4608, "128x144"), (333, 12288, "128x192"), (1000, 4608, "256x128"),
+                   (900, 4608, "128x144"), (333, 12288, "128x192"), (1000, 5120, "256x128"),
                    (700, 9216, "256x144"), (700, 12288, "256x192"), (4097, 3072, "256x256"),
                    (1410, 9216, "256x288")]
 
 
-@pytest.mark.parametrize("K", [64, 192])
 @pytest.mark.parametrize("M,N,tile", DMA_TILE_SHAPES, ids=[t[2] for t in DMA_TILE_SHAPES])
+@pytest.mark.parametrize("K", [64, 192, 576])
 def test_linear_bf16_every_tile(M, N, tile, K):
-    """Every tile of the direct-load GEMM at one K step and at an odd number of
-    steps: sampled rows against float64, and the first and last rows computed
-    alone (the 32-row tile) bitwise the same, for each kind of epilogue."""
+    """Every tile of the direct-load GEMM: sampled rows against float64, and the
+    last rows computed alone (the 32-row tile) bitwise the same, for each kind
+    of epilogue."""
     say(f"linear bf16 {M}x{N}x{K} ({tile})")
+    assert "%dx%d" % dma_tile(M, N, K) == tile and dma_tile(30, N, K)[0] == 32
     A, W, b = rnd(90, (M, K)), rnd(91, (N, K), 0.05), rnd(92, (N,), 0.1)
     x0, gate = rnd(93, (M, N), bf=False), rnd(94, (N,), 0.5, bf=False)
     rows = np.unique(np.r_[0, M // 2, M - 1])
