@@ -348,6 +348,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   // Slower or equal for 256 x 144 (one wave's 32 x 144: 27.1 -> 27.9 us) and 256
   // x 288 (its registers spill).
   constexpr bool ROLL = BM == 256 && (BN == 192 || BN == 128) && NW == 8;
+  static_assert(!ROLL || (!XT::on && ST <= 3), "the rolling loop's waits");
   if constexpr (ROLL) {
     // this lane's byte offset in a 16-row fragment (the swizzle depends on the
     // row within it alone); half-step 1 flips bit 6
@@ -400,8 +401,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
       half0(so);
       // stage t + 1 landed
       if (ST == 2 || t + 2 >= KT) wait_vmcnt<0>();
-      else if (ST == 3 || t + 3 >= KT) wait_vmcnt<BPW>();
-      else wait_rounds<BPW>(min(ST - 2, KT - 2 - t));
+      else wait_vmcnt<BPW>();
       block_barrier();
       const uint32_t sn = so == (ST - 1) * STAGE * 2 ? 0 : so + STAGE * 2;
       uint32_t ao = fo + (sn + wao), bo = fo + (sn + wbo);
@@ -411,7 +411,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
 #pragma unroll
       for (int j = 0; j < S; ++j) b[j] = rd(bo, j);
       const bool more = t + ST < KT;
-      if (XT::on && t + 2 == KT) xattn_prefetch();
 #pragma unroll
       for (int j = S; j < TN; ++j) {
         column(j, a1);
@@ -427,7 +426,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
       }
       so = sn;
     }
-    if (XT::on && KT == 1) xattn_prefetch();
     half0(so);
 #pragma unroll
     for (int j = S; j < TN; ++j) column(j, a1);
