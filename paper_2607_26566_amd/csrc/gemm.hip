@@ -929,16 +929,20 @@ hipError_t launch_gemm_f32(const float* A, int lda, const float* W, int ldw, con
   const bool dma = K % 32 == 0 && lda % 4 == 0 && ldw % 4 == 0 && al(A) && al(W) &&
                    (size_t)4 * M * lda < 0x7fffffff && (size_t)4 * N * ldw < 0x7fffffff;
   if (!dma) {
-    if ((long)M * N <= 4096 * 1024)
+    // 64 x 64 tiles from two per CU on (4096 x 1024 x 1001: 146 us, 205 on 32 x
+    // 32; 1024 x 1024 x 1001, one per CU: 81 against 55)
+    if ((long)((M + 63) / 64) * ((N + 63) / 64) < 512)
       return gemm_f32_dispatch<1, 1, false>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
     return gemm_f32_dispatch<2, 2, false>(A, lda, W, ldw, bias, M, N, K, kind, epi, vec_ok, st);
   }
-  // The CU with the most tiles decides: its tiles' K steps cost the larger of
-  // their matrix time (64 clocks per 16 x 16 x 4 MFMA group of the four waves:
-  // 256 per 32 x 32 of the tile) and their loads at ~20 bytes per clock.
+  // The CU with the most tiles decides: the matrix time of its tiles, which is
+  // their area.  (Charging their loads too, at 20 bytes per clock, takes larger
+  // tiles and was slower at 1024 rows and fewer: 1024 x 3456 x 1152 79 against
+  // 72 us, 333 x 2048 x 2048 43 against 32; faster only at some shapes of 2048
+  // rows, 2048 x 3456 x 1152 138 against 157.)
   auto cost = [&](long bm, long bn) {
     const long tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    return ((tiles + 255) / 256) * std::max(bm * bn / 4, (bm + bn) * 128 / 32);
+    return (tiles + 255) / 256 * bm * bn;
   };
   const long c22 = cost(64, 64), c12 = cost(32, 64), c11 = cost(32, 32);
   if (c22 <= c12 && c22 <= c11)
