@@ -29,6 +29,7 @@
 // attn_f32_kernel: fp32 online softmax on the fp32 matrix cores, for the fp32
 // model.
 #include <algorithm>
+#include <type_traits>
 
 #include "t2i_internal.h"
 #include "xattn_tile.h"
@@ -724,7 +725,9 @@ __global__ __launch_bounds__(NW * 64, (R > 1 ? 8 : (HD <= 72 ? 16 : 12)) / NW) v
 // tail of 8 by float2.  Bound by the matrix cores and, with one wave per SIMD
 // at 1024 queries x 16 heads, by the softmax between them: 80 us there at head
 // dimension 72, against 1186 for one thread per query with vector FMAs (64
-// queries x 2 heads: 7.1 against 81 us).
+// queries x 2 heads: 7.1 against 81 us).  A tile of at most 16 keys takes one
+// group of MFMAs instead of four: 32 sequences of one query, 16 heads of 128,
+// 20.1 -> 12.4 us (one thread per query 14.4).
 template <int HD>
 __global__ __launch_bounds__(256) void attn_f32_kernel(AttnMap map, int heads,
                                                        const float* __restrict__ Q, int ldq,
@@ -812,67 +815,74 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnMap map, int heads,
     tile_of(t, beg, left);
     if (t + 1 < nt) fetch(t + 1);
 
-    f32x4 sc[4];
+    // NG: 16-key groups of the tile; only the first one where it holds no more
+    // keys (the others would add nothing)
+    auto tile = [&](auto groups) {
+      constexpr int NG = decltype(groups)::value;
+      f32x4 sc[NG];
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt) sc[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int kt = 0; kt < NG; ++kt) sc[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < DF; ++c) {
-      f32x4 kf[4];
+      for (int c = 0; c < DF; ++c) {
+        f32x4 kf[NG];
 #pragma unroll
-      for (int kt = 0; kt < 4; ++kt) kf[kt] = *(const f32x4*)&Ks[(kt * 16 + fr) * P + c * 16 + g * 4];
+        for (int kt = 0; kt < NG; ++kt) kf[kt] = *(const f32x4*)&Ks[(kt * 16 + fr) * P + c * 16 + g * 4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-          sc[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kt][e], qf[c][e], sc[kt], 0, 0, 0);
-    }
-    if (TAIL) {
-      float kf[4][2];
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt) {
-        const float* kp = &Ks[(kt * 16 + fr) * P + DF * 16 + g * 2];
-        kf[kt][0] = kp[0];
-        kf[kt][1] = kp[1];
+          for (int kt = 0; kt < NG; ++kt)
+            sc[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kt][e], qf[c][e], sc[kt], 0, 0, 0);
       }
+      if (TAIL) {
+        float kf[NG][2];
 #pragma unroll
-      for (int e = 0; e < 2; ++e)
+        for (int kt = 0; kt < NG; ++kt) {
+          const float* kp = &Ks[(kt * 16 + fr) * P + DF * 16 + g * 2];
+          kf[kt][0] = kp[0];
+          kf[kt][1] = kp[1];
+        }
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-          sc[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kt][e], qt[e], sc[kt], 0, 0, 0);
-    }
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int kt = 0; kt < NG; ++kt)
+            sc[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kt][e], qt[e], sc[kt], 0, 0, 0);
+      }
 
-    float mx = m;
+      float mx = m;
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
+      for (int kt = 0; kt < NG; ++kt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        sc[kt][r] = kt * 16 + g * 4 + r < left ? sc[kt][r] * scale : -INFINITY;
-        mx = fmaxf(mx, sc[kt][r]);
-      }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-    const float corr = expf(m - mx);
-    m = mx;
-    float sum = 0.f;
+        for (int r = 0; r < 4; ++r) {
+          sc[kt][r] = kt * 16 + g * 4 + r < left ? sc[kt][r] * scale : -INFINITY;
+          mx = fmaxf(mx, sc[kt][r]);
+        }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+      const float corr = expf(m - mx);
+      m = mx;
+      float sum = 0.f;
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
+      for (int kt = 0; kt < NG; ++kt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        sc[kt][r] = expf(sc[kt][r] - mx);
-        sum += sc[kt][r];
-      }
-    l = l * corr + sum;
+        for (int r = 0; r < 4; ++r) {
+          sc[kt][r] = expf(sc[kt][r] - mx);
+          sum += sc[kt][r];
+        }
+      l = l * corr + sum;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
+      for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
+      for (int kt = 0; kt < NG; ++kt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float* vp = &Vs[(kt * 16 + g * 4 + r) * P + fr];
+        for (int r = 0; r < 4; ++r) {
+          const float* vp = &Vs[(kt * 16 + g * 4 + r) * P + fr];
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-          o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vp[dt * 16], sc[kt][r], o[dt], 0, 0, 0);
-      }
+          for (int dt = 0; dt < DT; ++dt)
+            o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vp[dt * 16], sc[kt][r], o[dt], 0, 0, 0);
+        }
+    };
+    if (left > 16) tile(std::integral_constant<int, 4>{});
+    else tile(std::integral_constant<int, 1>{});
   }
   l += __shfl_xor(l, 16, kWave);
   l += __shfl_xor(l, 32, kWave);

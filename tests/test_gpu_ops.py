@@ -274,10 +274,11 @@ def test_linear_f32_tiles(M, N, K):
 @pytest.mark.parametrize("d", [8, 32, 64, 72, 128])
 def test_attention_f32_tiles(d):
     """Every head size: sequences of one query, of a query tile and one more,
-    key counts around the 64-key tile, two key segments."""
+    key counts around the 64-key tile and the 16 keys of its groups, two key
+    segments."""
     say(f"attention f32 d {d}")
     H, w = 3, 3 * d
-    lens = [1, 64, 65, 127, 200]
+    lens = [1, 16, 17, 64, 65, 80, 81, 127, 200]
     seqs, seg2, row = [], [], 0
     for i, n in enumerate(lens):
         seqs.append((row, n, row, n))
