@@ -1540,6 +1540,27 @@ t2i_status t2i_op_attention(int32_t dtype, int32_t heads, int32_t head_dim, int3
   return T2I_OK;
 }
 
+int t2i_test_attention_plan(int heads, int n, const int* q_len, const int* k_start,
+                            const int* k_len, const int* k2_start, const int* k2_len, int* waves,
+                            int* ordered, int* runs) {
+  if (heads < 1 || n < 1 || n > kMaxSeq) return 0;
+  AttnMap m;
+  std::memset(&m, 0, sizeof(m));
+  m.n = n;
+  for (int s = 0; s < n; ++s) {
+    m.q_len[s] = q_len[s];
+    m.k_start[s] = k_start[s];
+    m.k_len[s] = k_len[s];
+    m.k2_start[s] = k2_start ? k2_start[s] : 0;
+    m.k2_len[s] = k2_len ? k2_len[s] : 0;
+  }
+  attention_tiles(m, true, heads, 0);
+  *waves = m.waves;
+  *ordered = m.ordered;
+  *runs = m.n;
+  return 1;
+}
+
 t2i_status t2i_op_cross_attention(int32_t dtype, int32_t heads, int32_t head_dim, int32_t n_seq,
                                   const int32_t* q_start, const int32_t* q_len,
                                   const int32_t* k_start, const int32_t* k_len, const void* q,

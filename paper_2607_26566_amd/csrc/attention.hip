@@ -124,11 +124,15 @@ __device__ __forceinline__ void decode_ordered(const AttnMap& m, int heads, int 
   j = r - q * nt;
 }
 
+// ARRANGED: a launch whose sequences attention_tiles has merged or ordered (an
+// instance of its own: the reads of those tables, one more level of loads that
+// wait for each other, cost a plain launch up to 0.7 us).
+//
 // ROLE: 0 = self / joint attention, 1 = cross-attention to text (separate
 // instances, so that profiles tell them apart).  QS: Q arrives already
 // multiplied by scale_log2 (the model's projections write it so, rounding the
 // scaled value once), else the scale is applied in fp32 to each score.
-template <int HD, int NW, int ST, int ROLE, bool QS>
+template <int HD, int NW, int ST, int ROLE, bool QS, bool ARRANGED>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_bf16_kernel(AttnMap map, int heads,
                                                            const bf16* __restrict__ Q, int ldq,
                                                            const bf16* __restrict__ K, int ldk,
@@ -163,8 +167,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_bf16_kernel(AttnMap map,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int hh, s, j;
-  constexpr bool ARRANGED = ROLE == 0 && NW > 2;   // (attention_tiles leaves 2-wave launches as they come)
-  if (ARRANGED && map.ordered && heads % 8 == 0)
+  if (ARRANGED && map.ordered)
     decode_ordered(map, heads, blockIdx.x, hh, s, j);
   else
     decode_tile<ROLE == 1>(map, heads, xcd_remap_attn(blockIdx.x, gridDim.x), hh, s, j);
@@ -919,7 +922,7 @@ constexpr int attn_stages() {
 constexpr int kCrossWaves = 4, kCrossStages = 3;
 void attention_tiles(AttnMap& m, bool bf16_io, int heads, int role) {
   for (int s = 0; s < m.n; ++s) m.q2_start[s] = m.q2_len[s] = 0;
-  m.ordered = 0;
+  m.ordered = m.merged = 0;
   auto fill = [&](int bq) {
     int t = 0;
     for (int s = 0; s < m.n; ++s) {
@@ -1017,8 +1020,13 @@ void attention_tiles(AttnMap& m, bool bf16_io, int heads, int role) {
   // 2-wave workgroups are one short round, where the few extra scalar loads
   // cost more (1024 queries 21.6 -> 22.3 us).
   if (role == 0 && w > 2) {
+    const AttnMap plain = m;
     merge_runs();
-    fill(32 * w);
+    // Merging pays with fewer workgroups, or where 16 sequences and more become
+    // half as many to look through (16 x 256 + 77, 16 heads: 31 against 33 us);
+    // otherwise a plain launch is up to 2 % faster (300 and 2000 + 77).
+    m.merged = fill(32 * w) < wgs || (w == kAttnWaves && plain.n >= 16 && m.n < plain.n);
+    if (!m.merged) m = plain;
     order(w);
   }
   m.waves = w;
@@ -1039,9 +1047,9 @@ static hipError_t launch_hd(bool bf16_io, int role, int heads, const AttnMap& ma
     if ((size_t)2 * heads * HD * ldv > 0x7fffffff || (size_t)2 * (k_rows + 64) * ldk > 0x7fffffff)
       return hipErrorInvalidValue;
     const float scale_log2 = attn_q_scale(HD);
-#define T2I_ATT(NW_, ST_, R_)                                                                   \
-  hipLaunchKernelGGL((attn_bf16_kernel<HD, NW_, ST_, R_, QS>), dim3(tiles), dim3(NW_ * 64), 0, st, map, \
-                     heads, (const bf16*)q, ldq, (const bf16*)k, ldk, (const bf16*)v, ldv,       \
+#define T2I_ATT(NW_, ST_, R_, ARR_)                                                             \
+  hipLaunchKernelGGL((attn_bf16_kernel<HD, NW_, ST_, R_, QS, ARR_>), dim3(tiles), dim3(NW_ * 64), 0, \
+                     st, map, heads, (const bf16*)q, ldq, (const bf16*)k, ldk, (const bf16*)v, ldv, \
                      (bf16*)o, ldo, scale_log2)
     // smaller workgroups (2 or 4 waves) share a CU and use a 3-stage ring
     if (role == 1) {
@@ -1065,12 +1073,15 @@ static hipError_t launch_hd(bool bf16_io, int role, int heads, const AttnMap& ma
         hipLaunchKernelGGL((attn_cross_kernel<HD, kCrossWaves, QS, 1>), dim3(tiles),
                            dim3(kCrossWaves * 64), 0, st, map, heads, (const bf16*)q, ldq,
                            (const bf16*)k, ldk, (const bf16*)v, ldv, (bf16*)o, ldo, scale_log2);
-      } else if (map.waves == kCrossWaves) T2I_ATT(kCrossWaves, kCrossStages, 1);
+      } else if (map.waves == kCrossWaves) T2I_ATT(kCrossWaves, kCrossStages, 1, false);
       else return hipErrorInvalidValue;
     } else {
-      if (map.waves == kAttnWaves) T2I_ATT(kAttnWaves, attn_stages<HD>(), 0);
-      else if (map.waves == 4) T2I_ATT(4, 3, 0);
-      else if (map.waves == 2) T2I_ATT(2, 3, 0);
+      const bool arranged = map.merged || map.ordered;
+      if (map.waves == kAttnWaves && arranged) T2I_ATT(kAttnWaves, attn_stages<HD>(), 0, true);
+      else if (map.waves == kAttnWaves) T2I_ATT(kAttnWaves, attn_stages<HD>(), 0, false);
+      else if (map.waves == 4 && arranged) T2I_ATT(4, 3, 0, true);
+      else if (map.waves == 4) T2I_ATT(4, 3, 0, false);
+      else if (map.waves == 2 && !arranged) T2I_ATT(2, 3, 0, false);
       else return hipErrorInvalidValue;
     }
 #undef T2I_ATT

@@ -39,12 +39,13 @@ struct AttnMap {
   int q_start[kMaxSeq], q_len[kMaxSeq], k_start[kMaxSeq], k_len[kMaxSeq];
   int k2_start[kMaxSeq], k2_len[kMaxSeq];
   int tile_start[kMaxSeq + 1];
-  // Set by attention_tiles for self / joint attention.  A second run of query
-  // rows with the same keys (joint attention: a request's text rows and its
-  // image rows): its 32-query groups follow the first run's, so that a
+  // Set by attention_tiles for self / joint attention.  merged: a second run of
+  // query rows with the same keys (joint attention: a request's text rows and
+  // its image rows), whose 32-query groups follow the first run's, so that a
   // workgroup may hold groups of both.
+  int merged;
   int q2_start[kMaxSeq], q2_len[kMaxSeq];
-  // sequences by key count, most keys first; used where `ordered`
+  // ordered: sequences by key count, most keys first
   int ordered;
   int order[kMaxSeq];
 };
@@ -209,6 +210,12 @@ hipError_t launch_gemm_f32(const float* A, int lda, const float* W, int ldw, con
 // (host arithmetic only): the direct-load tile of a bf16 layer (0: it takes
 // register-staged tiles).
 extern "C" int t2i_test_dma_tile(int M, int N, int K, int kind, int* rows, int* columns);
+// How a bf16 self / joint attention launch is arranged: waves per workgroup,
+// whether the longest sequences go first, sequences after merging (0: bad
+// arguments).
+extern "C" int t2i_test_attention_plan(int heads, int n, const int* q_len, const int* k_start,
+                                       const int* k_len, const int* k2_start, const int* k2_len,
+                                       int* waves, int* ordered, int* runs);
 
 // Conditioning GEMMs: A fp32 [M, K], W fp32 or bf16 [N, K]; STORE or SILU.
 // Per-group operand table of a grouped launch (by value in the kernel

@@ -323,6 +323,18 @@ def run_attention(dtype, heads, d, seqs, q, k, v, seg2=None):
     return to_host(o)
 
 
+def attention_plan(heads, seqs, seg2):
+    """(waves per workgroup, longest sequences first, query sequences after
+    merging those with the same keys) of a self / joint launch."""
+    n = len(seqs)
+    arr = lambda v: (C.c_int * n)(*v)  # noqa: E731
+    got = [C.c_int() for _ in range(3)]
+    k2 = [arr([s[i] for s in seg2]) if seg2 else None for i in range(2)]
+    assert t2i.load().t2i_test_attention_plan(heads, n, arr([s[1] for s in seqs]), arr([s[2] for s in seqs]),
+                                              arr([s[3] for s in seqs]), *k2, *map(C.byref, got))
+    return tuple(g.value for g in got)
+
+
 def run_cross_attention(heads, d, seqs, q, k, v):
     """seqs: (q_start, q_len, k_start, k_len); bf16, V passed transposed."""
     lib = t2i.load()
@@ -762,15 +774,22 @@ def test_lora_merge_batch_equals_single_merges(dtype, n_out, n_in, rank):
         assert torch.equal(x, y)
 
 
-# (heads, head size, text keys, image lengths): launches of 8- and 4-wave
-# workgroups whose text and image queries share workgroups and whose longest
-# sequences go first; equal lengths; heads that are no multiple of 8
-ARRANGED = [(24, 128, 77, [1301, 437]), (16, 72, 40, [1500, 900]), (8, 64, 0, [2100, 333, 64]),
-            (16, 72, 24, [1200, 1200]), (12, 72, 33, [1500, 700])]
+# (heads, head size, text keys, image lengths, then what the launch is made of:
+# waves per workgroup, longest sequences first, query sequences once those with
+# the same keys share workgroups).  Merged for fewer workgroups and for fewer
+# sequences, sorted with and without a text, both, neither; 8 and 4 waves; heads
+# that are no multiple of 8 (never sorted); launches of 2 waves run as they come
+ARRANGED = [(24, 128, 77, [2451, 1037], 8, 0, 2), (16, 72, 0, [3952, 1024, 432, 2640, 120], 8, 1, 5),
+            (16, 72, 77, [120, 432, 1024, 2640, 3952], 8, 1, 5), (12, 72, 33, [2900, 2000], 8, 0, 2),
+            (16, 72, 20, [256] * 16, 8, 0, 16), (16, 72, 20, [2300, 2300], 8, 0, 4),
+            (24, 128, 77, [1301, 437], 4, 0, 2), (16, 72, 40, [1500, 900], 4, 1, 2),
+            (12, 72, 20, [1900, 1100], 4, 0, 2), (12, 72, 33, [1900, 1100], 4, 0, 4),
+            (16, 72, 24, [1200, 1200], 4, 0, 2), (8, 64, 0, [2100, 333, 64], 2, 0, 3),
+            (12, 72, 33, [1500, 700], 2, 0, 4)]
 
 
-@pytest.mark.parametrize("H,d,text,lens", ARRANGED)
-def test_attention_bf16_arranged_launches(H, d, text, lens):
+@pytest.mark.parametrize("H,d,text,lens,waves,ordered,runs", ARRANGED)
+def test_attention_bf16_arranged_launches(H, d, text, lens, waves, ordered, runs):
     """Joint sequences of unequal length: sampled rows against float64, and
     every sequence bitwise what it is alone."""
     say(f"attention bf16 arranged {H}x{d} text {text} lens {lens}")
@@ -783,6 +802,7 @@ def test_attention_bf16_arranged_launches(H, d, text, lens):
         else:
             seqs.append((img, n, img, n))
         row = img + (n + 7) // 8 * 8
+    assert attention_plan(H, seqs, seg2) == (waves, ordered, runs)
     q, k, v = (rnd(110 + i, (row, w)) for i in range(3))
     got = run_attention(_lib.T2I_BF16, H, d, seqs, q, k, v, seg2 or None)
     for i, (q0, nq, k0, nk) in enumerate(seqs):
