@@ -674,20 +674,19 @@ __global__ __launch_bounds__(256) void lora_merge_kernel(int n_out, int n_in, in
 }
 
 // bf16 LoRA merge on MFMA, bound by reading and writing W.  A workgroup of 4
-// waves owns 64 columns of W and `steps` x 128 rows: it transposes its 64
-// columns of A through LDS once, every wave keeps them as MFMA fragments in
+// waves owns TN columns of W and `steps` x 128 rows: it transposes its columns
+// of A through LDS once, every wave keeps them as MFMA fragments in
 // registers (k contiguous, zero past `rank`), and then walks its rows 32 at a
 // time -- the rows of B straight from memory as the other operand, the product
 // on v_mfma_f32_32x32x16_bf16 (fp32 accumulation over the rank), turned from
 // the MFMA layout to row chunks in the wave's own part of LDS, added to W and
 // rounded once.  The next rows' W and B are fetched before the current ones
 // are finished.  Needs n_in % 8 == 0, ldw % 8 == 0 and 16-byte aligned W and A
-// (the launcher checks).  28 weights of 3456 x 1152: 138 -> 90 us at rank 64
-// (5.1 TB/s), 86 -> 73 at rank 16 (6.2 TB/s), 271 -> 149 at rank 128, against
+// (the launcher checks).  28 weights of 3456 x 1152: 139 -> 91 us at rank 64
+// (4.9 TB/s), 86 -> 72 at rank 16 (6.2 TB/s), 270 -> 116 at rank 128, against
 // one 64 x 128 tile per workgroup with both operands transposed through LDS.
-constexpr int kLoraTN = 64;
 
-template <int RK>
+template <int RK, int TN>
 __global__ __launch_bounds__(256) void lora_merge_mfma_kernel(int n_out, int n_in, int rank,
                                                               float alpha, LoraGroup g, int ldw,
                                                               int steps) {
@@ -696,35 +695,44 @@ __global__ __launch_bounds__(256) void lora_merge_mfma_kernel(int n_out, int n_i
   const bf16* __restrict__ A = (const bf16*)g.A[blockIdx.z];
   const bf16* __restrict__ B = (const bf16*)g.B[blockIdx.z];
   constexpr int KP = RK + 8;        // LDS row pitch of A^T (bf16)
-  constexpr int PP = kLoraTN + 4;   // LDS row pitch of the product (fp32)
-  constexpr int ABYTES = kLoraTN * KP * 2, PBYTES = 4 * 32 * PP * 4;
+  constexpr int PP = TN + 4;   // LDS row pitch of the product (fp32)
+  constexpr int ABYTES = TN * KP * 2, PBYTES = 4 * 32 * PP * 4;
   __shared__ __attribute__((aligned(16))) char smem[ABYTES > PBYTES ? ABYTES : PBYTES];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int i0 = blockIdx.x * kLoraTN;
+  const int i0 = blockIdx.x * TN;
   const int l32 = lane & 31, hl = lane >> 5;
   const int o_begin = (blockIdx.y * 4 + wave) * 32 * steps, o_end = min(o_begin + 32 * steps, n_out);
   typedef bf16 bf16x8u __attribute__((ext_vector_type(8), aligned(2)));   // B's rows start anywhere
 
-  // W of rows o .. o + 31: four 16-byte chunks per lane, row 8 c + lane / 8,
-  // columns 8 (lane % 8) ..
-  const int wr = lane >> 3, wc = i0 + (lane & 7) * 8;
-  auto load_w = [&](int o, bf16x8 (&v)[4]) {
+  // W of rows o .. o + 31: NC 16-byte chunks per lane, row RC c + lane / CR,
+  // columns 8 (lane % CR) ..
+  constexpr int CR = TN / 8, RC = 64 / CR, NC = 32 / RC, NT = TN / 32;
+  const int wr = lane / CR, wc = i0 + (lane % CR) * 8;
+  auto load_w = [&](int o, bf16x8 (&v)[NC]) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int r = o + 8 * c + wr;
+    for (int c = 0; c < NC; ++c) {
+      const int r = o + RC * c + wr;
       v[c] = bf16x8{};
       if (r < o_end && wc < n_in) v[c] = *(const bf16x8*)(W + (size_t)r * ldw + wc);
     }
   };
   auto load_b = [&](int o, bf16x8 (&v)[RK / 16]) {
-    const bf16* p = B + (size_t)min(o + l32, n_out - 1) * rank + 8 * hl;
+    const int row = min(o + l32, n_out - 1);
+    const bf16* p = B + (size_t)row * rank + 8 * hl;
 #pragma unroll
     for (int k = 0; k < RK / 16; ++k) {
       v[k] = bf16x8{};
       const int kk = 16 * k + 8 * hl;
       if (kk + 8 <= rank) {
         v[k] = *(const bf16x8u*)(p + 16 * k);
+      } else if (RK == 16 && kk < rank && (long)(n_out - row) * rank >= kk + 8) {
+        // a small rank would spend its time on single elements: one load that
+        // runs on into the rows after this one, whose values are dropped
+        v[k] = *(const bf16x8u*)(p + 16 * k);
+#pragma unroll
+        for (int j = 1; j < 8; ++j)
+          if (kk + j >= rank) v[k][j] = (bf16)0.f;
       } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -732,7 +740,7 @@ __global__ __launch_bounds__(256) void lora_merge_mfma_kernel(int n_out, int n_i
       }
     }
   };
-  bf16x8 wv[4], bv[RK / 16];
+  bf16x8 wv[NC], bv[RK / 16];
   if (o_begin < o_end) {
     load_w(o_begin, wv);
     load_b(o_begin, bv);
@@ -740,8 +748,8 @@ __global__ __launch_bounds__(256) void lora_merge_mfma_kernel(int n_out, int n_i
   // A^T [64][KP], zero past rank / the matrix edge: a thread takes 8 rows k of
   // one column chunk at a time, so that LDS is written 16 bytes of one column
   bf16* At = (bf16*)smem;
-  for (int e = tid; e < (RK / 8) * (kLoraTN / 8); e += 256) {
-    const int k = e / (kLoraTN / 8) * 8, c = (e % (kLoraTN / 8)) * 8;
+  for (int e = tid; e < (RK / 8) * (TN / 8); e += 256) {
+    const int k = e / (TN / 8) * 8, c = (e % (TN / 8)) * 8;
     bf16x8 r[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -757,9 +765,9 @@ __global__ __launch_bounds__(256) void lora_merge_mfma_kernel(int n_out, int n_i
     }
   }
   __syncthreads();
-  bf16x8 af[2][RK / 16];
+  bf16x8 af[NT][RK / 16];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int k = 0; k < RK / 16; ++k)
       af[t][k] = *(const bf16x8*)(At + (32 * t + l32) * KP + 16 * k + 8 * hl);
@@ -767,37 +775,39 @@ __global__ __launch_bounds__(256) void lora_merge_mfma_kernel(int n_out, int n_i
 
   float* Ps = (float*)smem + wave * 32 * PP;
   for (int o = o_begin; o < o_end; o += 32) {
-    f32x16 acc[2] = {f32x16{}, f32x16{}};
+    f32x16 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = f32x16{};
 #pragma unroll
     for (int k = 0; k < RK / 16; ++k)
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < NT; ++t)
         acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[t][k], bv[k], acc[t], 0, 0, 0);
     // lane: row l32, columns 32 t + 8 q + 4 hl .. + 3
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         *(f32x4*)&Ps[l32 * PP + 32 * t + 8 * q + 4 * hl] =
             f32x4{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
-    bf16x8 wn[4];
+    bf16x8 wn[NC];
     if (o + 32 < o_end) {
       load_b(o + 32, bv);
       load_w(o + 32, wn);
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const float* pr = &Ps[(8 * c + wr) * PP + (lane & 7) * 8];
+    for (int c = 0; c < NC; ++c) {
+      const float* pr = &Ps[(RC * c + wr) * PP + (lane % CR) * 8];
       const f32x4 p0 = *(const f32x4*)pr, p1 = *(const f32x4*)(pr + 4);
       bf16x8 y;
 #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = (bf16)fmaf(alpha, j < 4 ? p0[j] : p1[j - 4], (float)wv[c][j]);
-      const int r = o + 8 * c + wr;
+      const int r = o + RC * c + wr;
       if (r < o_end && wc < n_in) *(bf16x8*)(W + (size_t)r * ldw + wc) = y;
     }
     if (o + 32 < o_end)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) wv[c] = wn[c];
+      for (int c = 0; c < NC; ++c) wv[c] = wn[c];
   }
 }
 
@@ -835,18 +845,27 @@ hipError_t launch_lora_merge_group(bool bf16_io, int n, int n_out, int n_in, int
   for (int i = 0; i < n; ++i)
     vec = vec && (uintptr_t)g.W[i] % 16 == 0 && (uintptr_t)g.A[i] % 16 == 0;
   if (vec) {
-    // 32-row steps per wave: several (they share the transposed A) while that
-    // leaves 1024 workgroups or more
-    const long tiles = (long)((n_in + kLoraTN - 1) / kLoraTN) * ((n_out + 127) / 128) * n;
-    const int steps = tiles >= 8192 ? 4 : tiles >= 2048 ? 2 : 1;
-    dim3 grid((n_in + kLoraTN - 1) / kLoraTN, (n_out + 128 * steps - 1) / (128 * steps), n);
-#define T2I_LORA_MF(RK_)                                                                       \
-  hipLaunchKernelGGL((lora_merge_mfma_kernel<RK_>), grid, dim3(256), 0, st, n_out, n_in, rank, \
-                     alpha, g, ldw, steps)
-    if (rank <= 16) T2I_LORA_MF(16);
-    else if (rank <= 32) T2I_LORA_MF(32);
-    else if (rank <= 64) T2I_LORA_MF(64);
-    else T2I_LORA_MF(128);
+    // 32-row steps per wave, which share the transposed A: two from 1024
+    // workgroups of two steps on; four from 2048 workgroups of four where the
+    // transposed A is large (28 x 3456 x 1152 at rank 128 136 us, 149 with two;
+    // at rank 16 93 against 89 with two, from memory).
+    const long tiles = (long)((n_in + 63) / 64) * ((n_out + 127) / 128) * n;
+    const int steps = tiles >= 8192 && rank > 32 ? 4 : tiles >= 2048 ? 2 : 1;
+    // Rows of 256 bytes instead of 128 per workgroup for large wide weights of
+    // a small rank, whose time is W's alone (from memory at rank 8: 15 x 1152 x
+    // 4096 64.6 us against 67, 8 x 12288 x 3072 244 against 262; 15 x 4608 x
+    // 1152 67.2 against 65.8).
+    const bool wide = rank <= 16 && n_in >= 2048 && tiles >= 8192;
+    const int cols = wide ? 128 : 64;
+    dim3 grid((n_in + cols - 1) / cols, (n_out + 128 * steps - 1) / (128 * steps), n);
+#define T2I_LORA_MF(RK_, TN_)                                                                  \
+  hipLaunchKernelGGL((lora_merge_mfma_kernel<RK_, TN_>), grid, dim3(256), 0, st, n_out, n_in,  \
+                     rank, alpha, g, ldw, steps)
+    if (wide) T2I_LORA_MF(16, 128);
+    else if (rank <= 16) T2I_LORA_MF(16, 64);
+    else if (rank <= 32) T2I_LORA_MF(32, 64);
+    else if (rank <= 64) T2I_LORA_MF(64, 64);
+    else T2I_LORA_MF(128, 64);
 #undef T2I_LORA_MF
     return hipGetLastError();
   }

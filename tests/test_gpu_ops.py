@@ -818,9 +818,11 @@ def test_attention_bf16_arranged_launches(H, d, text, lens, waves, ordered, runs
 
 
 @pytest.mark.parametrize("n,n_out,n_in,rank", [(1, 2600, 264, 7), (40, 400, 1160, 3), (2, 1, 8, 1),
-                                               (20, 1030, 1152, 100), (1, 33, 72, 127)])
+                                               (20, 1030, 1152, 100), (1, 33, 72, 127),
+                                               (64, 400, 2056, 5), (64, 399, 2056, 16)])
 def test_lora_merge_strips(n, n_out, n_in, rank):
-    """Row steps per wave, ranks that are no multiple of 8, edges of rows and columns."""
+    """Row steps per wave, workgroups of 64 and (64 large wide weights) 128
+    columns, ranks that are no multiple of 8, edges of rows and columns."""
     from oracle import lora
     Ws = [rnd(120, (n_out, n_in), 0.05), rnd(121, (n_out, n_in), 0.05)]
     As = [rnd(122, (rank, n_in), 0.05), rnd(123, (rank, n_in), 0.05)]
@@ -837,3 +839,23 @@ def test_lora_merge_strips(n, n_out, n_in, rank):
         assert np.all(np.abs(got - ref) <= np.maximum(np.abs(ref), np.abs(got)) * 2.0 ** -8 + 1e-6)
     for i in range(2, n):
         assert torch.equal(dW[i], dW[i % 2])
+
+
+@pytest.mark.parametrize("rank", [1, 3, 13])
+def test_lora_merge_keeps_rows_apart(rank):
+    """A row of B with infinities and NaN changes no row of W but its own: a
+    row's vector load runs on into the rows after it."""
+    n_out, n_in = 70, 136
+    W, A, B = rnd(126, (n_out, n_in), 0.05), rnd(127, (rank, n_in), 0.05), rnd(128, (n_out, rank), 0.05)
+    bad = B.copy()
+    bad[[9, n_out - 1]] = np.inf
+    bad[40] = np.nan
+    out = []
+    for b in (B, bad):
+        w = to_dev(W, "bf16")
+        t2i.lora_merge(w, to_dev(A, "bf16"), to_dev(b, "bf16"), 0.7)
+        torch.cuda.synchronize()
+        out.append(to_host(w))
+    keep = np.setdiff1d(np.arange(n_out), [9, 40, n_out - 1])
+    assert np.array_equal(out[0][keep], out[1][keep])
+    assert not np.isfinite(out[1][[9, 40, n_out - 1]]).all()
