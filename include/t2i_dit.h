@@ -131,7 +131,10 @@ size_t t2i_cache_state_bytes(const t2i_dit_config* cfg, int32_t n_req,
  *             life (t2i_dit_rebind_weights replaces them).
  *   workspace device buffer of ws_bytes >= t2i_dit_workspace_bytes(cfg),
  *             256-byte aligned, borrowed for the handle's life.
- * Touches no device memory; `stream` is unused and may be NULL.
+ * Touches no device memory; `stream` is unused and may be NULL.  The handle
+ * holds about a kilobyte of page-locked host memory for cache checks,
+ * so that no later call allocates; it may be created and destroyed while a
+ * stream is being captured.
  */
 t2i_status t2i_dit_init(const t2i_dit_config* cfg, const void* const* weights,
                         void* workspace, size_t ws_bytes, void* stream,
