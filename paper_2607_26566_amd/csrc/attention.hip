@@ -1014,11 +1014,11 @@ void attention_tiles(AttnMap& m, bool bf16_io, int heads, int role) {
   }
   // The launches of larger workgroups are arranged for their ends: runs merged,
   // longest sequences first (24 heads of 77 + 2451 and 77 + 1037 joint queries
-  // 168 -> 135 us, 16 heads of 3952 + 2640 + 1024 + 432 + 120 139 -> 132, of
-  // 120 + 1700 and 120 + 900 38.0 -> 29.9; 3 x 256 + 3 x 1024 + 2 x 4096, whose
-  // end would be the same, keep their order: sorted 200 -> 204).  Those of
-  // 2-wave workgroups are one short round, where the few extra scalar loads
-  // cost more (1024 queries 21.6 -> 22.3 us).
+  // 160 -> 129 us, 16 heads of 120 + 1700 and 120 + 900 42 -> 36, of 3952 + 1024
+  // + 432 + 2640 + 120 142 -> 134; 3 x 256 + 3 x 1024 + 2 x 4096, whose end would
+  // be the same, keep their order: 197).  Those of 2-wave workgroups are one
+  // short round, where the few extra scalar loads cost more (1024 queries 21.6
+  // -> 22.3 us).
   if (role == 0 && w > 2) {
     const AttnMap plain = m;
     merge_runs();

@@ -429,8 +429,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 
 // Number of K slices (1 = no split) for a layer whose caller allows
 // splitting: narrow outputs (N <= 4096) against K >= 2048, one slice per
-// 1024 columns, at most 4.  It depends on the layer's shape only, never on
-// M, so a row's result does not depend on how many rows share the launch.
+// 1024 columns, at most 4.  It depends on the layer's shape only.  The launcher
+// drops the split from 2048 rows on, and where the workspace does not hold the
+// slices: a row's sums are those of any other row count on the same side of
+// that line, and differ across it in their last bits.
 static int splitk_factor(int N, int K) {
   if (N > 4096 || K < 2048) return 1;
   int s = std::min(4, K / 1024);
@@ -508,7 +510,9 @@ hipError_t launch_gemm_bf16(const bf16* A, int lda, const bf16* W, int ldw, cons
 }
 
 bool gemm_bf16_groupable(int M, int N, int kind) {
-  // the shapes launch_gemm_bf16 runs on register-staged tiles without split-K
+  // a grouped launch runs the register-staged tiles, with the sums of the single
+  // launches; from 2048 rows on a launch of direct-load tiles fills the chip by
+  // itself
   return M > 0 && N > 0 && !(M >= 2048 && (N % 144 == 0 || N % 128 == 0) && kind != EPI_SILU) &&
          (kind == EPI_STORE || kind == EPI_SPLIT_VT);
 }

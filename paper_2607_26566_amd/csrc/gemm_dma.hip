@@ -1,6 +1,6 @@
 // bf16 MFMA GEMM fed by direct HBM->LDS loads (gfx950 buffer_load_dwordx4 ... lds).
 //
-// y = A W^T + b for the DiT's projections at large M.  A workgroup owns a
+// y = A W^T + b for the projections of any row count.  A workgroup owns a
 // BM x BN output tile; its waves (WGM x WGN) each own a (BM/WGM) x (BN/WGN)
 // quadrant of 16x16 MFMA tiles (v_mfma_f32_16x16x32_bf16, fp32 accumulation).
 // K advances 64 at a time through a ring of ST LDS stages (see launch_gemm_dma
@@ -344,7 +344,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(
   // loads into the freed stage follow one or two per column.  Same MFMAs in the
   // same order.  256 x 192: 4096 x 3072 x 3072 72.9 -> 70.8 us, 3600 x 3072 x
   // 12288 267 -> 252 (from memory), 256 x 128: 2048 x 3072 x 3072 46.2 -> 41;
-  // 4096 x 3072 x 12288 277 either way when its operands come from memory.
+  // 4096 x 3072 x 12288 0.4 - 0.8 % slower (278 -> 280) when its operands come
+  // from memory.
   // Slower or equal for 256 x 144 (one wave's 32 x 144: 27.1 -> 27.9 us) and 256
   // x 288 (its registers spill).
   constexpr bool ROLL = BM == 256 && (BN == 192 || BN == 128) && NW == 8;

@@ -1334,7 +1334,8 @@ int cache_partial_blocks(const ReqMap& rm) {
 }
 
 // NI: float4 per lane (D <= 256 NI); NW: waves, each with 16 / NW rows in turn
-// (16 waves leave a lane 128 registers: too few for two rows of 3072 columns)
+// (16 waves leave a lane 128 registers: too few for two rows of 3072 columns,
+// 36 us at 4096 of them; 8 waves 32)
 template <int NI, int NW>
 __global__ __launch_bounds__(64 * NW) void cache_signal_kernel(
     const float* __restrict__ x0, ReqMap rm, const float* __restrict__ mod, int ld_mod,
